@@ -36,6 +36,7 @@
 #define PK_CT_STRIDE 132     // floats per row of the fp32 output tile in LDS
 #define PK_HT_STRIDE 136     // halves per row of the SwiGLU output tile in LDS
 #define PK_MAX_BYTES 0xF0000000ull
+#define PK_GROUP_Z 4         // row blocks of a group in the grouped tile order
 
 #define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
@@ -93,6 +94,7 @@ struct PackedParams {
     uint32_t a_bytes;   // size of each activation matrix in bytes (range check)
     int M, K, ksteps, chunks, splits, epilogue;
     int tiles, zblocks;  // n-tiles, row blocks
+    int group_z;         // 1: grouped tile order (many row blocks)
     void *out;
     f16_t *out_lo;       // SwiGLU epilogue, optional: second half term of the result, half(y - half(y)), same layout as out
     int64_t ldc;
@@ -131,14 +133,33 @@ __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_pa
     const int K = p.K;
 
     // ---- workgroup id -> (n-tile, K split, row block).  Workgroups whose ids are congruent mod 8 share an
-    //      XCD and its L2: the row blocks of one (tile, split) -- which stream the same weights -- get ids
-    //      8 apart, so the weights come from HBM once and from that L2 for the other row blocks.
-    const int ts_total = p.tiles * p.splits;
+    //      XCD and its L2.  Few row blocks: the row blocks of one (tile, split) -- which stream the same weights -- get ids
+    //      8 apart, so the weights come from HBM once and from that L2 for the other row blocks.  Many row blocks
+    //      (p.group_z, prefill): an XCD walks its share of the tiles in groups of PK_GROUP_Z row blocks, so that its 64 resident
+    //      workgroups form a block of 4 x 16 tiles and share both operands in L2.  (One column tile at a time would have every
+    //      XCD read all activation rows once per tile: 12 GB from memory in 2.6 ms at 16384 rows.  16384 rows, two terms,
+    //      N = 12288, K = 4096: 2622 -> 2423-2510 us; O 921 -> 882, down 2369 -> 2272, one-term gate/up 2547 -> 2450-2525.  Groups
+    //      of 8: level but down 2338; of 16 and 32: as before or slower.)
     const int id = blockIdx.x;
-    const int ts = (id / (8 * p.zblocks)) * 8 + (id & 7);
-    const int zb = (id % (8 * p.zblocks)) >> 3;
-    if (ts >= ts_total) return;  // padding of the id space (whole workgroup, before any barrier)
-    const int tile = ts % p.tiles, split = ts / p.tiles;
+    int tile, split, zb;
+    if (p.group_z) {
+        const int total = p.tiles * p.zblocks;
+        const int at = (id & 7) * ((total + 7) >> 3) + (id >> 3);
+        if ((id >> 3) >= ((total + 7) >> 3) || at >= total) return;  // padding of the id space (whole workgroup, before any barrier)
+        const int group = at / (PK_GROUP_Z * p.tiles);
+        const int in = at - group * PK_GROUP_Z * p.tiles;
+        const int gz = p.zblocks - group * PK_GROUP_Z < PK_GROUP_Z ? p.zblocks - group * PK_GROUP_Z : PK_GROUP_Z;
+        tile = in / gz;
+        zb = group * PK_GROUP_Z + in % gz;
+        split = 0;
+    } else {
+        const int ts_total = p.tiles * p.splits;
+        const int ts = (id / (8 * p.zblocks)) * 8 + (id & 7);
+        zb = (id % (8 * p.zblocks)) >> 3;
+        if (ts >= ts_total) return;  // padding of the id space (whole workgroup, before any barrier)
+        tile = ts % p.tiles;
+        split = ts / p.tiles;
+    }
     const int m0 = zb * BM;
     const int Mloc = p.M - m0 < BM ? p.M - m0 : BM;
 
@@ -417,7 +438,8 @@ static void launch_p2(PackedParams &p, hipStream_t st) {
         attr_set = true;
     }
     p.zblocks = ceil_div(p.M, BM);
-    int ids = ceil_div(p.tiles * p.splits, 8) * 8 * p.zblocks;
+    p.group_z = p.splits == 1 && p.zblocks >= 2 * PK_GROUP_Z ? 1 : 0;
+    int ids = p.group_z ? ceil_div(p.tiles * p.zblocks, 8) * 8 : ceil_div(p.tiles * p.splits, 8) * 8 * p.zblocks;
     if constexpr (NB == 1 && RC == 2) {
         if (p.cand_val) {  // the LM head with a fused greedy choice
             static bool cand_attr_set = false;

@@ -266,6 +266,25 @@ def test_gemm_packed_f32(ops, M, K, rows, splits, nb, terms, rpw):
     assert np.abs(got - ref).max() <= tol, (np.abs(got - ref).max(), tol)
 
 
+# row blocks of 128 (or 32): one below, at and above the count from which tiles are walked in groups of row blocks; tile counts that
+# do not divide by the 8 XCDs, a last group of fewer row blocks
+@pytest.mark.parametrize("M,K,rows,nb,terms,rpw", [(7 * 128, 136, (300,), 2, 2, 128), (8 * 128, 72, (1000, 72, 40), 1, 1, 128),
+                                                   (9 * 128 + 70, 136, (1400,), 2, 2, 128), (33 * 32 + 1, 200, (260,), 1, 2, 32)])
+def test_gemm_packed_many_row_blocks(ops, M, K, rows, nb, terms, rpw):
+    step(f"gemm_packed many row blocks M={M} K={K} rows={rows} nb={nb} terms={terms} rows_per_wg={rpw}")
+    A = randn_f16((M, K), 220 + M)
+    A_lo = randn_f16((M, K), 221 + M) * 2.0 ** -11 if terms == 2 else None
+    Ws = [randn_bf16((r, K), 230 + i + r, std=0.05) for i, r in enumerate(rows)]
+    N = sum(rows)
+    out = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
+    ops.gemm_packed(A, [pack(ops, w) for w in Ws], rows, K, out, N, A_lo=A_lo, epilogue=0, nb=nb, rows_per_wg=rpw, depth=2)
+    torch.cuda.synchronize()
+    a = np64(A) + (np64(A_lo) if terms == 2 else 0.0)
+    ref = np.concatenate([orc.linear(bits(w), a) for w in Ws], axis=1)
+    tol = 2e-6 * np.sqrt(K) * (np.abs(ref).max() + 1.0)
+    assert np.abs(np64(out) - ref).max() <= tol      # (a NaN left by a tile that no workgroup took fails this too)
+
+
 @pytest.mark.parametrize("M,K,V,two", [(4, 256, 1000, False), (128, 512, 32000, False), (200, 256, 1024, True), (5, 136, 128256, False),
                                        (130, 264, 3000, True)])
 def test_lm_head_with_fused_greedy_choice(ops, M, K, V, two):
