@@ -68,7 +68,8 @@ int rl_op_gemm_tiled_packed(const uint16_t *A, const uint16_t *A_lo, int64_t lda
                             int32_t rows2, int32_t M, int32_t K, void *out, int64_t ldc, int32_t epilogue, void *hip_stream);
 
 /* QKV projection of a prefill with the rotary embedding and the cache append in its epilogue (what a prefill of a model
- * with head_dim 128 and rotary style 1 runs): [q | k | v] = (A + A_lo) [Wq; Wk; Wv]^T by the large-M kernel, row m being
+ * with head_dim 128 and rotary style 1 runs when no fragment-order copies are attached; with copies it runs
+ * rl_op_gemm_packed_rope): [q | k | v] = (A + A_lo) [Wq; Wk; Wv]^T by the large-M kernel, row m being
  * sequence b0 + m / T at position m % T; q and k rotated with rope_tab (fp32 [S, 64, 2]); q stored as half [M, Hq*128],
  * k and v rows rounded to half and stored into kc / vc (half [n_seq][Hkv][S][128]).  Bit for bit what rl_op_gemm (fp32
  * output) followed by rl_op_rope_append stores.  RL_GEN_E_SHAPE where the fused form does not apply (head_dim, style,
@@ -87,6 +88,16 @@ int rl_op_gemm_rope(const uint16_t *A, const uint16_t *A_lo, int64_t lda, const 
  * memory, so the projection below fetches weights straight into the registers the matrix cores read. */
 size_t rl_op_packed_weight_bytes(int32_t N, int32_t K);
 int rl_op_pack_weights(const uint16_t *W, uint16_t *P, int32_t N, int32_t K, void *hip_stream);
+
+/* rl_op_gemm_rope over packed weights: what a prefill of more than 256 rows runs when copies are attached.  Any prompt length T;
+ * bit for bit what rl_op_gemm_packed (fp32 output, nb 2, 128 rows per workgroup) followed by rl_op_rope_append stores.
+ * table (optional, DEVICE int32 [n_seq, ceil(S / page_size)]): kc / vc (and the scales) are page pools, page_size as in
+ * rl_op_decode_attention_paged; entries are not checked.  d_valid (optional, DEVICE int32 per sequence): rows at positions
+ * d_valid[b] and beyond are not stored into the cache.  RL_GEN_E_SHAPE for another head_dim or rotary style, 128 rows or fewer. */
+int rl_op_gemm_packed_rope(const uint16_t *A, const uint16_t *A_lo, int64_t lda, const uint16_t *Pq, const uint16_t *Pk, const uint16_t *Pv,
+                           int32_t Hq, int32_t Hkv, int32_t hd, int32_t M, int32_t K, int32_t T, int32_t b0, const float *rope_tab,
+                           int32_t rope_style, int32_t S, uint16_t *q_f16, uint16_t *kc, uint16_t *vc, float *kscale, float *vscale,
+                           uint16_t *q_f16_lo, const int32_t *table, int32_t page_size, const int32_t *d_valid, void *hip_stream);
 
 /* Projection over packed weights (the decode step's form of rl_op_gemm; same meaning of rows_i, M, K, lda,
  * out, ldc, split_stride, splits and epilogue).  A_lo: optional second term of the activations (f16 [M, K],

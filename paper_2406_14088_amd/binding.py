@@ -96,6 +96,7 @@ def lib():
         "rl_op_add_rmsnorm": (C.c_int, [vp, vp, i32, sz, vp, f32, vp, vp, i32, i32, vp]),
         "rl_op_gemm": (C.c_int, [vp, vp, i64, vp, vp, vp, i32, i32, i32, i32, i32, vp, i64, sz, i32, i32, i32, vp, vp]),
         "rl_op_gemm_rope": (C.c_int, [vp, vp, i64, vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp, i32, i32, vp, vp, vp, vp, vp, vp, vp]),
+        "rl_op_gemm_packed_rope": (C.c_int, [vp, vp, i64, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp, i32, i32, vp, vp, vp, vp, vp, vp, vp, i32, vp, vp]),
         "rl_op_gemm_packed_swiglu_halves": (C.c_int, [vp, i64, vp, vp, i32, i32, i32, vp, i64, i32, vp, vp]),
         "rl_op_gemm_tiled_packed": (C.c_int, [vp, vp, i64, vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp, i64, i32, vp]),
         "rl_op_packed_weight_bytes": (sz, [i32, i32]),
@@ -130,7 +131,7 @@ EXPORTED_SYMBOLS = (
     "rl_gen_pack_weights", "rl_gen_prefill", "rl_gen_prefill_ragged", "rl_gen_set_eos", "rl_gen_read_state", "rl_gen_compact", "rl_gen_logprobs", "rl_gen_values",
     "rl_gen_decode_step", "rl_gen_generate", "rl_gen_set_graph", "rl_gen_set_qkv_terms", "rl_gen_set_sampling", "rl_gen_reset", "rl_gen_state", "rl_gen_destroy", "rl_gen_last_error",
     "rl_gen_profile", "rl_gen_profile_read", "rl_gen_kernel_class_name", "rl_op_embed", "rl_op_add_rmsnorm", "rl_op_gemm",
-    "rl_op_gemm_rope", "rl_op_gemm_tiled_packed", "rl_op_packed_weight_bytes", "rl_op_pack_weights", "rl_op_gemm_packed", "rl_op_lm_head_argmax_ws_floats", "rl_op_lm_head_argmax", "rl_op_gemm_packed_swiglu_halves", "rl_op_build_rope_table", "rl_op_rope_append", "rl_op_decode_attention", "rl_op_decode_attention_ws_floats", "rl_op_decode_attention_noalloc", "rl_op_decode_attention_paged", "rl_op_decode_attention_fused",
+    "rl_op_gemm_rope", "rl_op_gemm_tiled_packed", "rl_op_packed_weight_bytes", "rl_op_pack_weights", "rl_op_gemm_packed", "rl_op_gemm_packed_rope", "rl_op_lm_head_argmax_ws_floats", "rl_op_lm_head_argmax", "rl_op_gemm_packed_swiglu_halves", "rl_op_build_rope_table", "rl_op_rope_append", "rl_op_decode_attention", "rl_op_decode_attention_ws_floats", "rl_op_decode_attention_noalloc", "rl_op_decode_attention_paged", "rl_op_decode_attention_fused",
     "rl_op_prefill_attention", "rl_op_argmax", "rl_op_sample", "rl_op_logprob_gather", "rl_op_copy")
 
 
@@ -481,6 +482,13 @@ class _Ops:
                                        T, b0, rope_tab.data_ptr(), rope_style, S, q_f16.data_ptr(), kc.data_ptr(), vc.data_ptr(), _ptr(kscale), _ptr(vscale),
                                        _ptr(q_f16_lo), _stream()),
                  "rl_op_gemm_rope")
+
+    def gemm_packed_rope(self, A, Ps, Hq, Hkv, hd, M, K, T, b0, rope_tab, rope_style, S, q_f16, kc, vc, A_lo=None, kscale=None, vscale=None,
+                         q_f16_lo=None, table=None, page_size=0, d_valid=None):
+        pq, pk, pv = (x.data_ptr() for x in Ps)
+        self._ck(lib().rl_op_gemm_packed_rope(A.data_ptr(), _ptr(A_lo), A.stride(0), pq, pk, pv, Hq, Hkv, hd, M, K, T, b0, rope_tab.data_ptr(),
+                                              rope_style, S, q_f16.data_ptr(), kc.data_ptr(), vc.data_ptr(), _ptr(kscale), _ptr(vscale),
+                                              _ptr(q_f16_lo), _ptr(table), page_size, _ptr(d_valid), _stream()), "rl_op_gemm_packed_rope")
 
     def gemm_packed_swiglu_halves(self, A, Pg, Pu, F, K, out, ldc, M=None, depth=0, out_lo=None):
         M = A.shape[0] if M is None else M

@@ -105,6 +105,7 @@ struct PackedParams {
     int32_t *cand_idx;
     int cand_tiles;
     int no_store;
+    RopeEpilogue rope;  // EPI_ROPE
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t pk_rsrc(const void *p, uint32_t bytes) {
@@ -119,7 +120,8 @@ constexpr int pk_wgs_per_cu(int NB, int MT, int RC) { return pk_regs(NB, MT, RC)
 // because the cache policy is an immediate of the load instruction and a branch per load would cut the loop into pieces.
 // CAND: the plain-store epilogue also leaves the candidates of a greedy choice (PackedParams::cand_val); a template
 // parameter so that the projections that never ask for them keep their code and registers.
-template <int NB, int TERMS, int MT, int RC, bool SW, bool CAND = false>
+// ROPE: the epilogue of a prefill's QKV projection (EPI_ROPE), likewise a kernel of its own.
+template <int NB, int TERMS, int MT, int RC, bool SW, bool CAND = false, bool ROPE = false>
 __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_packed_kernel(PackedParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int BM = 32 * MT;               // activation rows per workgroup
@@ -371,6 +373,78 @@ __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_pa
                     p.cand_idx[at] = bi;
                 }
             }
+            if constexpr (ROPE) {
+                // The 128 columns of the pass are one head of q, k or v, and its rows lie in LDS: 16 lanes take a row, lane c the
+                // elements 4 c .. + 3 and their partners 64 + 4 c .. + 3, so the table row, the head row and its low term move
+                // as whole 128-byte lines and the row maximum is four shuffles.  The arithmetic is rope_append_kernel's,
+                // operation for operation.  While one workgroup is here the other one of the compute unit multiplies; the
+                // tile kernel's epilogue, one workgroup per compute unit, adds 0.5-0.65 ms to a call (16384 rows of the 7B
+                // shape, two terms, block-scaled rows: 3350 us there, 2770 here; the plain fp32 store 2464).
+                if (ncols > 0) {
+                    const RopeEpilogue &rp = p.rope;
+                    const int head = n_first >> 7, c = t & 15;
+                    const bool bs = rp.map.kscale != nullptr;
+#pragma unroll 4
+                    for (int i = 0; i < BM / 16; ++i) {
+                        const int ml = (t >> 4) + 16 * i;
+                        if (ml >= Mloc) continue;  // whole groups of 16 lanes
+                        const int m = m0 + ml;
+                        const int seq = m / rp.T, pos = m - seq * rp.T;
+                        f32x4_t a = *reinterpret_cast<const f32x4_t *>(ct + ml * PK_CT_STRIDE + 4 * c);
+                        f32x4_t b = *reinterpret_cast<const f32x4_t *>(ct + ml * PK_CT_STRIDE + 64 + 4 * c);
+                        if (seg != 2) {
+                            const float *tab = rp.rope_tab + (size_t)(pos < rp.S ? pos : rp.S - 1) * 128 + 8 * c;
+                            const f32x4_t t0 = *reinterpret_cast<const f32x4_t *>(tab), t1 = *reinterpret_cast<const f32x4_t *>(tab + 4);
+                            const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const float ra = __fmaf_rn(a[e], cs[e], -__fmul_rn(b[e], sn[e]));
+                                const float rb = __fmaf_rn(b[e], cs[e], __fmul_rn(a[e], sn[e]));
+                                a[e] = ra; b[e] = rb;
+                            }
+                        }
+                        if (seg == 0) {
+                            const size_t at = ((size_t)m * rp.Hq + head) * 128 + 4 * c;
+                            const u32x2_t ha = {pack_f16x2(a.x, a.y), pack_f16x2(a.z, a.w)}, hb = {pack_f16x2(b.x, b.y), pack_f16x2(b.z, b.w)};
+                            *reinterpret_cast<u32x2_t *>(rp.q_f16 + at) = ha;
+                            *reinterpret_cast<u32x2_t *>(rp.q_f16 + at + 64) = hb;
+                            if (rp.q_f16_lo) {
+                                const u32x2_t la = {pack_f16x2_lo(a.x, a.y, ha.x), pack_f16x2_lo(a.z, a.w, ha.y)};
+                                const u32x2_t lb = {pack_f16x2_lo(b.x, b.y, hb.x), pack_f16x2_lo(b.z, b.w, hb.y)};
+                                *reinterpret_cast<u32x2_t *>(rp.q_f16_lo + at) = la;
+                                *reinterpret_cast<u32x2_t *>(rp.q_f16_lo + at + 64) = lb;
+                            }
+                            continue;
+                        }
+                        float am = 0.f;  // row maximum (block-scaled rows)
+                        if (bs) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) am = fmaxf(am, fmaxf(fabsf(a[e]), fabsf(b[e])));
+#pragma unroll
+                            for (int o = 1; o < 16; o <<= 1) am = fmaxf(am, __shfl_xor(am, o, 64));
+                        }
+                        bool keep = pos < rp.S;
+                        if (rp.d_valid) {  // rows past a sequence's own length never reach the cache
+                            int nv = rp.d_valid[rp.b0 + seq];
+                            nv = nv < 1 ? 1 : (nv > rp.T ? rp.T : nv);
+                            keep = keep && pos < nv;
+                        }
+                        if (!keep) continue;
+                        const size_t rowi = kv_row_index(rp.map, rp.b0 + seq, head, rp.Hkv, rp.S, pos);
+                        f16_t *dst = (seg == 1 ? rp.kc : rp.vc) + rowi * 128 + 4 * c;
+                        if (bs) {
+                            const float inv = kv_inv_of(am);
+                            *reinterpret_cast<u32x2_t *>(dst) = u32x2_t{pack_i16x2(kv_quant(a.x, inv), kv_quant(a.y, inv)), pack_i16x2(kv_quant(a.z, inv), kv_quant(a.w, inv))};
+                            *reinterpret_cast<u32x2_t *>(dst + 64) = u32x2_t{pack_i16x2(kv_quant(b.x, inv), kv_quant(b.y, inv)), pack_i16x2(kv_quant(b.z, inv), kv_quant(b.w, inv))};
+                            if (c == 0) (seg == 1 ? rp.map.kscale : rp.map.vscale)[rowi] = kv_scale_of(am);
+                        } else {
+                            *reinterpret_cast<u32x2_t *>(dst) = u32x2_t{pack_f16x2(a.x, a.y), pack_f16x2(a.z, a.w)};
+                            *reinterpret_cast<u32x2_t *>(dst + 64) = u32x2_t{pack_f16x2(b.x, b.y), pack_f16x2(b.z, b.w)};
+                        }
+                    }
+                }
+                continue;
+            }
             // 32 lanes x float4 = one 512-byte output row; 8 rows per pass
 #pragma unroll
             for (int i = 0; i < BM / 8; ++i) {
@@ -440,6 +514,18 @@ static void launch_p2(PackedParams &p, hipStream_t st) {
     p.zblocks = ceil_div(p.M, BM);
     p.group_z = p.splits == 1 && p.zblocks >= 2 * PK_GROUP_Z ? 1 : 0;
     int ids = p.group_z ? ceil_div(p.tiles * p.zblocks, 8) * 8 : ceil_div(p.tiles * p.splits, 8) * 8 * p.zblocks;
+    if constexpr (NB == 2 && MT == 4 && RC == 2 && !SW) {
+        if (p.epilogue == EPI_ROPE) {
+            static bool rope_attr_set = false;
+            if (!rope_attr_set) {
+                (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_packed_kernel<NB, TERMS, MT, RC, SW, false, true>),
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+                rope_attr_set = true;
+            }
+            gemm_packed_kernel<NB, TERMS, MT, RC, SW, false, true><<<ids, PK_THREADS, lds, st>>>(p);
+            return;
+        }
+    }
     if constexpr (NB == 1 && RC == 2) {
         if (p.cand_val) {  // the LM head with a fused greedy choice
             static bool cand_attr_set = false;
@@ -746,6 +832,12 @@ bool gemm_packed_single_launch(int N, int K) {
     return (size_t)ceil_div(N, 32) * 32 * ((size_t)ceil_div(K, 16) * 32) < PK_MAX_BYTES;
 }
 
+// EPI_ROPE from the copies: whole heads of 128 columns per matrix, rotary style 1, more rows than one row block (any prompt length:
+// every row finds its own sequence and position), operands below the 32-bit offsets of the kernel.
+bool gemm_packed_rope_supported(int M, int K, int64_t lda, int Hq, int hd, int rope_style) {
+    return hd == 128 && rope_style == 1 && M > 128 && ((size_t)M * lda + K) * 2 < PK_MAX_BYTES && gemm_packed_single_launch(Hq * hd, K);
+}
+
 void launch_gemm_packed(const PackedGemmArgs &a, hipStream_t st) {
     if (a.M <= 0) return;
     // 32-bit byte offsets inside the kernel: a packed matrix of PK_MAX_BYTES or more is walked in row slabs
@@ -775,9 +867,10 @@ void launch_gemm_packed(const PackedGemmArgs &a, hipStream_t st) {
         }
         return;
     }
-    PackedParams p;
+    PackedParams p = {};
     p.A = a.A;
     p.A_lo = a.A_lo;
+    if (a.epilogue == EPI_ROPE) p.rope = *a.rope;
     p.lda_bytes = (int)(a.lda * 2);
     p.a_bytes = (uint32_t)((((size_t)a.M - 1) * a.lda + a.K) * 2);
     p.M = a.M;

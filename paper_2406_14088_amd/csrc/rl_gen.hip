@@ -331,6 +331,20 @@ int project(rl_gen *h, int cls, const f16_t *A, const f16_t *A_lo, int64_t lda, 
     return 1;
 }
 
+// QKV projection of a prefill from the fragment-order copies: 128-row workgroups of the packed kernel, whose epilogue rotates q
+// and k and stores q and the cache rows.  16384 rows of the 7B shape: two terms and block-scaled rows 2770 us (tile kernel
+// 3350), one term and half rows 1436 (2232).
+void rope_projection_from_copies(const f16_t *A, const f16_t *A_lo, int64_t lda, int M, int K, const f16_t *Pq, const f16_t *Pk,
+                                 const f16_t *Pv, const RopeEpilogue &rp, hipStream_t st) {
+    PackedGemmArgs q;
+    q.A = A; q.A_lo = A_lo; q.lda = lda; q.M = M; q.K = K;
+    q.P[0] = Pq; q.P[1] = Pk; q.P[2] = Pv;
+    q.rows[0] = rp.Hq * 128; q.rows[1] = rp.Hkv * 128; q.rows[2] = rp.Hkv * 128;
+    q.out = nullptr; q.ldc = 0; q.split_stride = 0; q.splits = 1; q.epilogue = EPI_ROPE; q.rope = &rp;
+    q.nb = 2; q.rows_per_wg = 128; q.depth = 2;
+    launch_gemm_packed(q, st);
+}
+
 // Is the fragment-order kernel the faster one for the fused gate/up projection of M rows?  The row-major kernel runs
 // F / 64 workgroups that each own a compute unit, 128 rows at a time.  Measured crossovers: beyond 256 workgroups it needs
 // a second, partly empty round (34B shape at 64 rows: 192 against 137 us; 70B shape at 32 rows: 219 against 163 us);
@@ -437,21 +451,30 @@ bool run_layers(rl_gen *h, const int32_t *tokens, int nb, int T, int b0, bool de
         const KvMap map = h->kvmap(l);
         const bool pk = h->packed && M <= kSkinnyMaxM;
         const f16_t *hq_lo = terms == 2 ? h_lo : nullptr;
+        auto rope_epilogue = [&]() {
+            RopeEpilogue rp;
+            rp.rope_tab = h->rope(); rp.T = T; rp.b0 = b0; rp.Hq = s.n_heads; rp.Hkv = s.n_kv_heads; rp.S = s.max_seq;
+            rp.q_f16 = h->qbf(); rp.q_f16_lo = q_lo; rp.kc = h->kslab(l); rp.vc = h->vslab(l); rp.map = map; rp.d_valid = d_valid;
+            return rp;
+        };
         bool qkv_stored = false;  // q and the cache rows already written by the projection itself
         int ns;
         if (pk)  // both terms go through the same weight fragments into the same accumulators
             ns = project_packed(h, RL_GEN_K_GEMM_QKV, h->h(), hq_lo, d, M, d, h->pw[W_Q][l], qd, h->pw[W_K][l], kvd, h->pw[W_V][l],
                                 kvd, st);
-        else if (!decode && gemm_tiled_rope_supported(M, d, d, s.n_heads, s.n_kv_heads, s.head_dim, s.rope_style, T, hq_lo != nullptr) &&
+        else if (!decode && h->packed && gemm_packed_rope_supported(M, d, d, s.n_heads, s.head_dim, s.rope_style)) {
+            RopeEpilogue rp = rope_epilogue();
+            Scope sc(h, RL_GEN_K_GEMM_QKV, st);
+            rope_projection_from_copies(h->h(), hq_lo, d, M, d, h->pw[W_Q][l], h->pw[W_K][l], h->pw[W_V][l], rp, st);
+            qkv_stored = true;
+            ns = 0;
+        } else if (!decode && gemm_tiled_rope_supported(M, d, d, s.n_heads, s.n_kv_heads, s.head_dim, s.rope_style, T, hq_lo != nullptr) &&
                  (!hq_lo || (size_t)(hq_lo - h->h()) * 2 < 0x70000000ull)) {
             // prefill: the projection's epilogue rotates q and k and stores q and the cache rows itself
-            RopeEpilogue rp;
-            rp.rope_tab = h->rope(); rp.T = T; rp.b0 = b0; rp.Hq = s.n_heads; rp.Hkv = s.n_kv_heads; rp.S = s.max_seq;
-            rp.q_f16 = h->qbf(); rp.q_f16_lo = q_lo; rp.kc = h->kslab(l); rp.vc = h->vslab(l); rp.map = map; rp.d_valid = d_valid;
+            RopeEpilogue rp = rope_epilogue();
             GemmArgs a;
             a.A = h->h(); a.A_lo = hq_lo; a.lda = d; a.M = M; a.K = d;
             a.W[0] = h->lw[W_Q][l]; a.W[1] = h->lw[W_K][l]; a.W[2] = h->lw[W_V][l];
-            if (h->packed) { a.P[0] = h->pw[W_Q][l]; a.P[1] = h->pw[W_K][l]; a.P[2] = h->pw[W_V][l]; }
             a.rows[0] = qd; a.rows[1] = kvd; a.rows[2] = kvd;
             a.out = nullptr; a.ldc = 0; a.split_stride = 0; a.splits = 1; a.epilogue = EPI_ROPE; a.rope = &rp;
             {
@@ -1414,6 +1437,24 @@ int rl_op_gemm_rope(const uint16_t *A, const uint16_t *A_lo, int64_t lda, const 
     a.out = nullptr; a.ldc = 0; a.split_stride = 0; a.splits = 1; a.epilogue = EPI_ROPE; a.rope = &rp;
     if (Pq && Pk && Pv) { a.P[0] = Pq; a.P[1] = Pk; a.P[2] = Pv; }
     launch_gemm_tiled(a, reinterpret_cast<hipStream_t>(st));
+    RL_OP_RETURN();
+}
+
+int rl_op_gemm_packed_rope(const uint16_t *A, const uint16_t *A_lo, int64_t lda, const uint16_t *Pq, const uint16_t *Pk, const uint16_t *Pv,
+                           int32_t Hq, int32_t Hkv, int32_t hd, int32_t M, int32_t K, int32_t T, int32_t b0, const float *rope_tab,
+                           int32_t rope_style, int32_t S, uint16_t *q_f16, uint16_t *kc, uint16_t *vc, float *kscale, float *vscale,
+                           uint16_t *q_f16_lo, const int32_t *table, int32_t page_size, const int32_t *d_valid, void *st) {
+    if (!A || !Pq || !Pk || !Pv || !rope_tab || !q_f16 || !kc || !vc) return RL_GEN_E_NULL;
+    if ((kscale == nullptr) != (vscale == nullptr)) return RL_GEN_E_NULL;
+    if (M <= 0 || K <= 0 || K % 8 || lda % 8 || lda < K || Hq <= 0 || Hkv <= 0 || T <= 0 || b0 < 0 || S < T) return RL_GEN_E_SHAPE;
+    if (table && !page_shift_of(page_size)) return RL_GEN_E_SHAPE;
+    if (!gemm_packed_rope_supported(M, K, lda, Hq > Hkv ? Hq : Hkv, hd, rope_style)) return RL_GEN_E_SHAPE;
+    RopeEpilogue rp;
+    rp.rope_tab = rope_tab; rp.T = T; rp.b0 = b0; rp.Hq = Hq; rp.Hkv = Hkv; rp.S = S;
+    rp.q_f16 = q_f16; rp.q_f16_lo = q_f16_lo; rp.kc = kc; rp.vc = vc; rp.map = KvMap(); rp.d_valid = d_valid;
+    rp.map.kscale = kscale; rp.map.vscale = vscale;
+    if (table) { rp.map.table = table; rp.map.table_stride = ceil_div(S, page_size); rp.map.page_shift = page_shift_of(page_size); }
+    rope_projection_from_copies(A, A_lo, lda, M, K, Pq, Pk, Pv, rp, reinterpret_cast<hipStream_t>(st));
     RL_OP_RETURN();
 }
 

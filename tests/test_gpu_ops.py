@@ -1062,3 +1062,52 @@ def test_qkv_projection_with_rotary_epilogue_block_scaled_equals_the_two_kernels
         want = y if name == "v" else orc.rope(y, 11, 10000.0, 1)
         deq = got.cpu().numpy().astype(np.float64) * np64(sc)[:, None]
         assert (np.abs(deq - want) <= 0.51 * np64(sc)[:, None] + 2e-4).all(), name
+
+
+@pytest.mark.parametrize("Hq,Hkv,T,nseq,two,bs,page", [(2, 2, 40, 4, True, True, 0), (3, 1, 7, 37, False, False, 0), (8, 2, 33, 34, True, False, 16),
+                                                       (1, 1, 300, 1, True, True, 64)])
+def test_gemm_packed_rope_equals_projection_then_rope_append(ops, Hq, Hkv, T, nseq, two, bs, page):
+    """The fused epilogue stores the bits that the packed projection (fp32) followed by rope_append stores: prompts shorter and
+    longer than a row block, odd head counts (a last column tile of one head), paged pools; rows beyond a sequence's own
+    length stay out of the cache."""
+    step(f"packed rope heads={Hq}/{Hkv} T={T} nseq={nseq} two={two} bs={bs} page={page}")
+    hd, K, b0, S = 128, 200, 1, T + 9
+    M, n_all = nseq * T, (Hq + 2 * Hkv) * hd
+    A = randn_f16(((2 if two else 1) * M, K), 600 + T)
+    if two:
+        A[M:] *= 2.0 ** -11
+    A_lo = A[M:] if two else None
+    Ps = [pack(ops, randn_bf16((h * hd, K), 601 + i, 0.05)) for i, h in enumerate((Hq, Hkv, Hkv))]
+    tab = torch.empty((S, hd // 2, 2), dtype=torch.float32, device=DEV)
+    ops.build_rope_table(tab, S, hd, 10000.0)
+
+    def caches(n, rows):
+        kv = [torch.zeros((n, Hkv, rows, hd), dtype=torch.int16, device=DEV) for _ in range(2)]
+        sc = [torch.zeros((n, Hkv, rows), dtype=torch.float32, device=DEV) if bs else None for _ in range(2)]
+        return kv + sc, [torch.zeros((M, Hq * hd), dtype=torch.int16, device=DEV) for _ in range(2)]
+
+    part = torch.empty((M, n_all), dtype=torch.float32, device=DEV)
+    ops.gemm_packed(A[:M], Ps, (Hq * hd, Hkv * hd, Hkv * hd), K, part, n_all, A_lo=A_lo, M=M, nb=2, rows_per_wg=128, depth=2)
+    want, (q1, l1) = caches(b0 + nseq, S)
+    ops.rope_append(part, 1, M * n_all, M, T, b0, torch.zeros((1,), dtype=torch.int32, device=DEV), tab, 1, Hq, Hkv, hd, S, None, q1, want[0],
+                    want[1], kscale=want[2], vscale=want[3], q_f16_lo=l1 if bs else None)
+    valid = torch.tensor([T] * b0 + [T - (i * 3) % T for i in range(nseq)], dtype=torch.int32, device=DEV)
+    for d_valid in (None, valid):
+        per = -(-S // page) if page else 0
+        got, (q2, l2) = caches((b0 + nseq) * per, page) if page else caches(b0 + nseq, S)
+        order = torch.randperm((b0 + nseq) * per, generator=torch.Generator().manual_seed(3)) if page else None
+        table = order.to(torch.int32).to(DEV).reshape(b0 + nseq, per).contiguous() if page else None
+        ops.gemm_packed_rope(A[:M], Ps, Hq, Hkv, hd, M, K, T, b0, tab, 1, S, q2, got[0], got[1], A_lo=A_lo, kscale=got[2], vscale=got[3],
+                             q_f16_lo=l2 if bs else None, table=table, page_size=page, d_valid=d_valid)
+        torch.cuda.synchronize()
+        assert torch.equal(q1, q2) and torch.equal(l1, l2) and q1.abs().max() > 0
+        for w, g in zip(want, got):
+            if w is None:
+                continue
+            if page:   # pages back into sequence order: [seq, page index, head, row, ...] -> [seq, head, position, ...]
+                g = g[order.to(DEV)].reshape((b0 + nseq, per) + g.shape[1:]).transpose(1, 2).flatten(2, 3)[:, :, :S]
+            if d_valid is not None:
+                w = w.clone()
+                for b in range(b0 + nseq):
+                    w[b, :, int(valid[b]):] = 0
+            assert torch.equal(w, g) and g[b0:].abs().max() > 0
