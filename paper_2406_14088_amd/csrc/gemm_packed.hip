@@ -578,10 +578,10 @@ static void launch_pm(PackedParams &p, int mt, int depth, hipStream_t st) {
 // each chunk in ascending chunks, then half 0 + half 1 -- is that of the row-major kernel, and so are the results, bit for
 // bit.  One workgroup per compute unit (the register ring holds RC chunks of weight fragments: 8 KB each).
 #define PS_BK 128
-template <int RC, bool SW>
+template <int MT, int RC, bool SW>
 __global__ __launch_bounds__(PK_THREADS, 1) void gemm_packed_swiglu_halves_kernel(PackedParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int MT = 4, BM = 128, NBUF = 3;
+    constexpr int BM = 32 * MT, NBUF = 3;
     constexpr int XTILE = BM * 64 * 2;   // one 64-wide half of an activation chunk
     constexpr int XBUF = 2 * XTILE;
     const int t = threadIdx.x, lane = t & 63;
@@ -653,8 +653,8 @@ __global__ __launch_bounds__(PK_THREADS, 1) void gemm_packed_swiglu_halves_kerne
 
     auto body = [&](int c, int buf, auto slot_tag) {
         constexpr int SLOT = decltype(slot_tag)::value;
-        // the copy of chunk c was issued two trips ago, before that trip's 8 weight loads and the 16 loads of the last trip
-        constexpr int YOUNGER = 8 + 16;
+        // the copy of chunk c was issued two trips ago, before that trip's 8 weight loads and all loads of the last trip
+        constexpr int YOUNGER = 8 + 2 * MT + 8;
         __builtin_amdgcn_s_waitcnt((YOUNGER & 15) | (7 << 4) | (15 << 8) | ((YOUNGER >> 4) << 14));  // vmcnt(YOUNGER) only
         __builtin_amdgcn_s_barrier();  // chunk c has landed for every wavefront; the buffer of chunk c - 1 is free
         int nbuf = buf + NBUF - 1;
@@ -743,7 +743,7 @@ __global__ __launch_bounds__(PK_THREADS, 1) void gemm_packed_swiglu_halves_kerne
     const int ncols = rows - tile * 64;
     f16_t *const outs[2] = {reinterpret_cast<f16_t *>(p.out), p.out_lo};
 #pragma unroll
-    for (int i = 0; i < BM / 32; ++i) {
+    for (int i = 0; i < MT; ++i) {
         int m = rr + 32 * i;
         if (m < Mloc && c8 < ncols) {
             const size_t at = (size_t)(m0 + m) * p.ldc + tile * 64 + c8;
@@ -766,19 +766,19 @@ __global__ __launch_bounds__(PK_THREADS, 1) void gemm_packed_swiglu_halves_kerne
     }
 }
 
-template <int RC, bool SW>
+template <int MT, int RC, bool SW>
 static void launch_halves(PackedParams &p, hipStream_t st) {
-    size_t lds = (size_t)3 * 2 * 128 * 64 * 2;  // three chunk buffers; the epilogue's exchange area and first tile fit inside
-    const size_t epi = (size_t)2 * 2 * 4 * 16 * 64 * 4 + (size_t)2 * 128 * 72 * 2;  // exchange area + both output tiles
+    size_t lds = (size_t)3 * 2 * 32 * MT * 64 * 2;  // three chunk buffers
+    const size_t epi = (size_t)2 * 2 * MT * 16 * 64 * 4 + (size_t)2 * 32 * MT * 72 * 2;  // exchange area + both output tiles
     if (epi > lds) lds = epi;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_packed_swiglu_halves_kernel<RC, SW>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_packed_swiglu_halves_kernel<MT, RC, SW>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         attr_set = true;
     }
     int ids = ceil_div(p.tiles, 8) * 8 * p.zblocks;
-    gemm_packed_swiglu_halves_kernel<RC, SW><<<ids, PK_THREADS, lds, st>>>(p);
+    gemm_packed_swiglu_halves_kernel<MT, RC, SW><<<ids, PK_THREADS, lds, st>>>(p);
 }
 
 bool gemm_packed_swiglu_halves_supported(int F, int K) {
@@ -807,8 +807,10 @@ void launch_gemm_packed_swiglu_halves(const PackedGemmArgs &a, hipStream_t st) {
     p.zblocks = ceil_div(a.M, 128);
     if (p.tiles <= 0) return;
     const bool deep = a.depth != 2;
-    if (p.zblocks == 1) { if (deep) launch_halves<4, true>(p, st); else launch_halves<2, true>(p, st); }
-    else { if (deep) launch_halves<4, false>(p, st); else launch_halves<2, false>(p, st); }
+    if (a.M <= 32) { if (deep) launch_halves<1, 4, true>(p, st); else launch_halves<1, 2, true>(p, st); }
+    else if (a.M <= 64) { if (deep) launch_halves<2, 4, true>(p, st); else launch_halves<2, 2, true>(p, st); }
+    else if (p.zblocks == 1) { if (deep) launch_halves<4, 4, true>(p, st); else launch_halves<4, 2, true>(p, st); }
+    else { if (deep) launch_halves<4, 4, false>(p, st); else launch_halves<4, 2, false>(p, st); }
 }
 
 // Decomposition of a projection with fp32 partial outputs.  Measured inside whole decode steps of the 7B shape,

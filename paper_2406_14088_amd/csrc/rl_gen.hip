@@ -359,9 +359,9 @@ bool packed_swiglu_wins(int M, int ffn) { return M > 128 || ffn > 256 * 64 || (f
 bool swiglu_project(rl_gen *h, const f16_t *A, const f16_t *A_lo, f16_t *out_lo, int M, int l, hipStream_t st) {
     const bool copies = h->packed && l < h->packed_gu_layers;
     // Up to 128 rows and FFN widths up to 16384: the kernel that puts the K halves of each chunk on separate wavefronts (the
-    // row-major kernel's sums in its order, from the copies).  Measured against the other two at 128 / 64 rows: FFN 11008
-    // 46.6 us (row-major 52.2, packed 61); FFN 14336 54.0 / 49.7 us (packed 61 / 54.6, row-major 63 / 55.7).  Wider
-    // FFNs (K = 8192 shapes) and more rows stay with the packed kernel (34B shape at 64 rows: 137 against 160 us).
+    // row-major kernel's sums in its order, from the copies).  Against the packed kernel at 1 / 64 / 128 rows: FFN 11008
+    // 34 / 40 / 51 us (46 / 54 / 57); FFN 14336 40 / 45 / 55 us (49 / 57 / 60); the row-major kernel takes 52 and 63 us at 128
+    // rows.  Wider FFNs (K = 8192 shapes) and more rows stay with the packed kernel (34B shape at 64 rows: 137 against 160 us).
     if (copies && !A_lo && M <= 128 && h->s.ffn <= 256 * 64 && gemm_packed_swiglu_halves_supported(h->s.ffn, h->s.hidden)) {
         PackedGemmArgs q;
         q.A = A; q.A_lo = nullptr; q.lda = h->s.hidden; q.M = M; q.K = h->s.hidden;

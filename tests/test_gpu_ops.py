@@ -193,7 +193,8 @@ def test_gemm_tiled_from_fragment_order_copies_with_a_row_stride(ops):
 
 
 @pytest.mark.parametrize("M,K,F,depth", [(4, 256, 688, 4), (128, 512, 1000, 2), (256, 256, 72, 4), (128, 4096, 1100, 4), (77, 1000, 200, 2),
-                                          (200, 136, 96, 0)])
+                                          (200, 136, 96, 0), (1, 1000, 70, 2), (32, 136, 688, 2), (33, 264, 96, 2), (64, 512, 130, 4),
+                                          (65, 136, 96, 2)])
 def test_gemm_packed_swiglu_on_k_halves_equals_the_row_major_kernel(ops, M, K, F, depth):
     """Same column sums in the same order (K halves of each 128-wide chunk, ascending chunks, half 0 + half 1): the kernel
     over fragment-order copies stores the bits the row-major kernel stores; one row also against the oracle."""
@@ -1111,3 +1112,21 @@ def test_gemm_packed_rope_equals_projection_then_rope_append(ops, Hq, Hkv, T, ns
                 for b in range(b0 + nseq):
                     w[b, :, int(valid[b]):] = 0
             assert torch.equal(w, g) and g[b0:].abs().max() > 0
+
+
+@pytest.mark.parametrize("H,B", [(32, 63), (32, 64), (31, 67)])   # 2016, 2048 and 2077 items: wavefronts share an item, or take one each
+def test_decode_attention_around_the_sharing_of_items(ops, H, B):
+    step(f"decode attention, {H * B} items")
+    hd, S, lens = 64, 150, [0, 31, 32, 33, 127, 128, 149]     # trips of 32 rows: fewer, as many and more than four
+    kc, vc = randn_f16((B, H, S, hd), 701), randn_f16((B, H, S, hd), 702)
+    q = randn_f32((B, H * hd), 703, std=0.7)
+    d_len = torch.tensor([lens[b % len(lens)] for b in range(B)], dtype=torch.int32, device=DEV)
+    out = torch.zeros((B, H * hd), dtype=torch.float16, device=DEV)
+    ops.decode_attention(q, kc, vc, d_len, out, torch.empty(1, device=DEV), B, H, H, hd, S, 1, len_stride=1)
+    torch.cuda.synchronize()
+    qn, kn, vn, on = np64(q).reshape(B, H, hd), np64(kc), np64(vc), np64(out).reshape(B, H, hd)
+    for b in (*range(len(lens)), B - 1):
+        n = lens[b % len(lens)] + 1
+        for u in (0, 1, 2, 3, H - 1):
+            ref = orc.attend(qn[b, u], kn[b, u, :n], vn[b, u, :n])
+            assert (np.abs(on[b, u] - ref) <= 0.5 * F16_EPS * np.abs(ref) * 1.02 + 2e-5).all(), (b, u)
