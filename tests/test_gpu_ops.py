@@ -463,7 +463,7 @@ def test_decode_attention_fused_with_rope_and_append(ops, style, hd, Hq, Hkv, le
 
 
 @pytest.mark.parametrize("hd,Hq,Hkv", [(128, 4, 4), (128, 8, 2), (64, 4, 1)])
-@pytest.mark.parametrize("T", [1, 16, 100, 128, 129, 300])
+@pytest.mark.parametrize("T", [1, 16, 100, 300])
 def test_prefill_attention(ops, hd, Hq, Hkv, T):
     step(f"prefill attention hd={hd} Hq={Hq} Hkv={Hkv} T={T}")
     nb, b0, S, nseq = 2, 1, 320, 3
@@ -970,7 +970,7 @@ def test_decode_attention_at_long_context_lengths(ops, kind, length):
 
 
 @pytest.mark.parametrize("hd,Hq,Hkv", [(128, 4, 4), (128, 8, 2), (64, 4, 1)])
-@pytest.mark.parametrize("T", [1, 16, 100, 128, 129, 300])
+@pytest.mark.parametrize("T", [1, 16, 100, 300])
 def test_prefill_attention_block_scaled_rows_and_two_term_output(ops, hd, Hq, Hkv, T):
     """Prefill attention over int16 * scale rows: every element enters the matrix cores as hi + lo, so only q and the
     probabilities carry a half rounding."""
