@@ -419,7 +419,11 @@ int decode_attention_default_splits(int B, int Hkv, int S) {
 // batch 24, 2048 rows in 3 splits 139 -> 132.  From 2048 items (two wavefronts per SIMD) on the gain turns with the length (batch 64:
 // 384 rows 61.6 -> 66.8, 1024 rows 172 -> 164), and with several query heads per wavefront (more registers, more to merge) it
 // ends at 512 items (64/8 heads: 384 items 16.9 -> 15.2, 768 items 17.1 -> 20.9).
-static bool wavefronts_share_an_item(int n_items, int heads_per_wavefront) { return n_items < (heads_per_wavefront == 1 ? 2048 : 512); }
+// The order of a sequence's sums depends on it, so a generator decides once, for its capacity: a batch that shrinks keeps its bits.
+bool decode_attention_shares_items(int B, int Hq, int Hkv, int nsplit) {
+    const int g = Hq / Hkv, gt = decode_attention_group(g);
+    return (long)B * Hkv * (g / gt) * nsplit < (gt == 1 ? 2048 : 512);
+}
 
 template <int HD, int GT, int WS>
 static void launch_da(const float *q, f16_t *kc, f16_t *vc, const int32_t *d_len, int len_stride, f16_t *out, f16_t *out_lo, float *ws,
@@ -441,14 +445,14 @@ static void launch_da(const float *q, f16_t *kc, f16_t *vc, const int32_t *d_len
 }
 
 static void dispatch_da(const float *q, f16_t *kc, f16_t *vc, const int32_t *d_len, int len_stride, f16_t *out, f16_t *out_lo, float *ws,
-                        int B, int Hq, int Hkv, int hd, int S, int nsplit, const FusedQkv *fq, const KvMap &map, const int32_t *d_done,
-                        hipStream_t st) {
+                        int B, int Hq, int Hkv, int hd, int S, int nsplit, bool share, const FusedQkv *fq, const KvMap &map,
+                        const int32_t *d_done, hipStream_t st) {
     if (B <= 0) return;
     int g = Hq / Hkv;
     int gt = decode_attention_group(g);
 #define DA_CASE(HDV, GTV) \
     if (hd == HDV && gt == GTV) {                                                                                                    \
-        if (wavefronts_share_an_item(B * Hkv * (g / GTV) * nsplit, GTV))                                                              \
+        if (share)                                                                                                                   \
             launch_da<HDV, GTV, 4>(q, kc, vc, d_len, len_stride, out, out_lo, ws, B, Hq, Hkv, S, nsplit, fq, map, d_done, st);        \
         else                                                                                                                         \
             launch_da<HDV, GTV, 1>(q, kc, vc, d_len, len_stride, out, out_lo, ws, B, Hq, Hkv, S, nsplit, fq, map, d_done, st);        \
@@ -460,14 +464,14 @@ static void dispatch_da(const float *q, f16_t *kc, f16_t *vc, const int32_t *d_l
 }
 
 void launch_decode_attention(const float *q, const f16_t *kc, const f16_t *vc, const int32_t *d_len, int len_stride, f16_t *out,
-                             float *ws, int B, int Hq, int Hkv, int hd, int S, int nsplit, hipStream_t st, KvMap map,
+                             float *ws, int B, int Hq, int Hkv, int hd, int S, int nsplit, bool share, hipStream_t st, KvMap map,
                              const int32_t *d_done, f16_t *out_lo) {
     // many query heads per cache row: the matrix-core kernel (half and block-scaled rows)
     if (decode_attention_gqa_takes(Hq, Hkv, hd, map.kscale != nullptr)) {
         launch_decode_attention_gqa(q, kc, vc, d_len, len_stride, out, ws, B, Hq, Hkv, S, nsplit, st, map, d_done, out_lo);
         return;
     }
-    dispatch_da(q, const_cast<f16_t *>(kc), const_cast<f16_t *>(vc), d_len, len_stride, out, out_lo, ws, B, Hq, Hkv, hd, S, nsplit,
+    dispatch_da(q, const_cast<f16_t *>(kc), const_cast<f16_t *>(vc), d_len, len_stride, out, out_lo, ws, B, Hq, Hkv, hd, S, nsplit, share,
                 nullptr, map, d_done, st);
 }
 
@@ -476,7 +480,8 @@ void launch_decode_attention_fused(const float *qkv, int nsplit_qkv, size_t spli
                                    int Hkv, int hd, int S, int nsplit, hipStream_t st) {
     FusedQkv fq;
     fq.part = qkv; fq.nsplit = nsplit_qkv; fq.split_stride = split_stride; fq.rope_tab = rope_tab; fq.rope_style = rope_style;
-    dispatch_da(nullptr, kc, vc, d_len, len_stride, out, nullptr, ws, B, Hq, Hkv, hd, S, nsplit, &fq, KvMap(), nullptr, st);
+    dispatch_da(nullptr, kc, vc, d_len, len_stride, out, nullptr, ws, B, Hq, Hkv, hd, S, nsplit,
+                decode_attention_shares_items(B, Hq, Hkv, nsplit), &fq, KvMap(), nullptr, st);
 }
 
 void launch_decode_attention_merge(const float *ws, f16_t *out, int B, int Hq, int hd, int nsplit, hipStream_t st, f16_t *out_lo) {

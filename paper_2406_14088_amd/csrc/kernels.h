@@ -151,9 +151,10 @@ void gemm_packed_plan(int N, int K, int M, int *nb, int *rows_per_wg, int *split
 // ---- attention_decode.hip ------------------------------------------------------------------------
 // One new query per (sequence, query head) against cache rows 0 .. d_len[b * len_stride] (inclusive).
 // q fp32 [B, Hq*hd] (already rotated); kc/vc this layer's K and V areas (half) laid out as `map` says; out half
-// [B, Hq*hd].  ws: fp32 workspace of decode_attention_ws_floats(...) elements when nsplit > 1.
+// [B, Hq*hd].  ws: fp32 workspace of decode_attention_ws_floats(...) elements when nsplit > 1.  share: the four wavefronts of a
+// workgroup take a sequence's rows together (the vector kernel only; sums in another order), see decode_attention_shares_items.
 void launch_decode_attention(const float *q, const f16_t *kc, const f16_t *vc, const int32_t *d_len, int len_stride, f16_t *out,
-                             float *ws, int B, int Hq, int Hkv, int hd, int S, int nsplit, hipStream_t st, KvMap map = KvMap(),
+                             float *ws, int B, int Hq, int Hkv, int hd, int S, int nsplit, bool share, hipStream_t st, KvMap map = KvMap(),
                              const int32_t *d_done = nullptr,   // d_done (optional): sequences with a non-zero flag are skipped
                              f16_t *out_lo = nullptr);          // out_lo (optional): half(o - half(o)), second term of the output
 // Fused form: q, k, v of the new token are taken from the split-K partials of the QKV projection (each
@@ -175,6 +176,7 @@ void launch_decode_attention_merge(const float *ws, f16_t *out, int B, int Hq, i
 size_t decode_attention_ws_floats(int B, int Hq, int hd, int nsplit);
 int decode_attention_default_splits(int B, int Hkv, int S);
 int decode_attention_group(int g);  // query heads per wavefront for Hq/Hkv = g
+bool decode_attention_shares_items(int B, int Hq, int Hkv, int nsplit);
 
 // ---- attention_prefill.hip -----------------------------------------------------------------------
 // Causal attention over the T prompt positions of nb sequences whose K/V already sit in the cache.

@@ -171,6 +171,7 @@ struct rl_gen {
     unsigned char *work;
     WorkPlan wp;
     int nsplit_attn;
+    bool share_attn;  // decode attention: wavefronts share an item; from max_batch, as nsplit_attn
     int prec;      // resolved precision level (1..3)
     bool kv_i16;   // cache rows are 16-bit block-scaled fixed point; their fp32 scales follow all rows in the arena
     int B, len;
@@ -504,7 +505,7 @@ bool run_layers(rl_gen *h, const int32_t *tokens, int nb, int T, int b0, bool de
         if (decode) {
             Scope sc(h, RL_GEN_K_DECODE_ATTN, st);
             launch_decode_attention(h->qf32(), h->kslab(l), h->vslab(l), h->d_lens(), 1, h->attn(), h->attn_ws(), nb,
-                                    s.n_heads, s.n_kv_heads, s.head_dim, s.max_seq, h->nsplit_attn, st, map,
+                                    s.n_heads, s.n_kv_heads, s.head_dim, s.max_seq, h->nsplit_attn, h->share_attn, st, map,
                                     h->eos >= 0 ? h->d_done() : nullptr, attn_lo);  // ended sequences cost no cache traffic
         } else {
             Scope sc(h, RL_GEN_K_PREFILL_ATTN, st);
@@ -789,6 +790,7 @@ static int create_impl(const rl_gen_shape *shape, const rl_gen_weights *w, void 
     h->work = reinterpret_cast<unsigned char *>(work_arena);
     h->wp = wp;
     h->nsplit_attn = attn_splits(shape);
+    h->share_attn = decode_attention_shares_items(shape->max_batch, shape->n_heads, shape->n_kv_heads, h->nsplit_attn);
     h->prec = prec_level(shape);
     h->kv_i16 = kv_block_scaled(shape);
     h->B = 0; h->len = 0;
@@ -1584,8 +1586,8 @@ int rl_op_decode_attention(const float *q, const uint16_t *kc, const uint16_t *v
     if (len_stride != 0 && len_stride != 1) return RL_GEN_E_SHAPE;
     KvMap map;
     map.kscale = const_cast<float *>(kscale); map.vscale = const_cast<float *>(vscale);
-    launch_decode_attention(q, kc, vc, d_len, len_stride, out, ws, B, Hq, Hkv, hd, S, nsplit, reinterpret_cast<hipStream_t>(st), map,
-                            d_done, out_lo);
+    launch_decode_attention(q, kc, vc, d_len, len_stride, out, ws, B, Hq, Hkv, hd, S, nsplit,
+                            decode_attention_shares_items(B, Hq, Hkv, nsplit), reinterpret_cast<hipStream_t>(st), map, d_done, out_lo);
     RL_OP_RETURN();
 }
 
@@ -1611,7 +1613,7 @@ int rl_op_decode_attention_noalloc(const float *q, const uint16_t *kc, const uin
     KvMap map;
     map.kscale = const_cast<float *>(kscale); map.vscale = const_cast<float *>(vscale);
     launch_decode_attention(q, kc, vc, d_len, len_stride, out, reinterpret_cast<float *>(ws), B, Hq, Hkv, hd, S, nsplit,
-                            reinterpret_cast<hipStream_t>(st), map, d_done, out_lo);
+                            decode_attention_shares_items(B, Hq, Hkv, nsplit), reinterpret_cast<hipStream_t>(st), map, d_done, out_lo);
     RL_OP_RETURN();
 }
 
@@ -1628,8 +1630,8 @@ int rl_op_decode_attention_paged(const float *q, const uint16_t *k_pool, const u
     KvMap map;
     map.table = table; map.table_stride = table_stride; map.page_shift = shift;
     map.kscale = const_cast<float *>(kscale); map.vscale = const_cast<float *>(vscale);
-    launch_decode_attention(q, k_pool, v_pool, d_len, len_stride, out, ws, B, Hq, Hkv, hd, S, nsplit, reinterpret_cast<hipStream_t>(st),
-                            map);
+    launch_decode_attention(q, k_pool, v_pool, d_len, len_stride, out, ws, B, Hq, Hkv, hd, S, nsplit,
+                            decode_attention_shares_items(B, Hq, Hkv, nsplit), reinterpret_cast<hipStream_t>(st), map);
     RL_OP_RETURN();
 }
 

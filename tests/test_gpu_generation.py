@@ -928,6 +928,43 @@ def test_batch_compaction_after_the_end_token(cache, graph):
     assert worst <= LOGIT_TOL
 
 
+@pytest.mark.parametrize("kv_heads", [32, 8])
+def test_compaction_keeps_the_bits_where_decode_attention_changes_its_split(kv_heads):
+    """70 sequences are one wavefront per sequence and head (or per 4 query heads), fewer than 64 alone would be four: what a
+    generator runs follows its capacity, so the logits of the sequences that stay are those of the uncompacted run, bit for bit."""
+    from paper_2406_14088_amd import Generator
+    shape = ModelShape(1, 2048, 32, kv_heads, 64, 512, 24)
+    B, P, G = 70, 40, 5
+    W = make_weights(shape, 65, device="cpu", std=0.05)
+    Wg = {k: ([t.to(DEV) for t in v] if isinstance(v, list) else v.to(DEV)) for k, v in W.items()}
+    prompts = make_prompts(Workload("t", 65, shape, B, P, G)).to(DEV)
+    gen = Generator(shape, Wg, B, P + G)
+    first = gen.prefill(prompts)[1].cpu().numpy()
+    eos = int(np.bincount(first, minlength=shape.vocab).argmax())           # the most frequent first token ends its sequences
+    gen.reset()
+    gen.set_eos(eos)
+    _, t = gen.prefill(prompts)
+    start, want = t.clone(), []
+    for _ in range(G):
+        lg, t = gen.decode_step(t)
+        want.append(lg.clone())
+        t = t.clone()
+    gen.reset()
+    _, t = gen.prefill(prompts)
+    assert torch.equal(t, start)
+    t = t.clone()
+    kept = gen.compact(t)
+    assert 1 < len(kept) < 64, len(kept)
+    live = torch.arange(len(kept), device=DEV)                             # rows that have not ended since (ended rows are unspecified)
+    for i in range(G):
+        lg, nxt = gen.decode_step(t[: len(kept)].contiguous())
+        assert torch.equal(lg[live].view(torch.int32), want[i][kept][live].view(torch.int32)), i
+        live = live[nxt[live] != eos]
+        assert len(live) > 1
+        t = nxt.clone()
+    gen.close()
+
+
 def test_batch_compaction_when_nobody_or_everybody_has_ended():
     from paper_2406_14088_amd import Generator, RlGenError
     wl = PRESETS["tiny"]
