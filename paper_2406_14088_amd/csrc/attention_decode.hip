@@ -275,7 +275,12 @@ __global__ __launch_bounds__(DA_THREADS) void decode_attention_kernel(
             float mnew = mx[gh];
 #pragma unroll
             for (int u = 0; u < DA_U; ++u) mnew = fmaxf(mnew, sc[gh][u]);
-            if (mnew == -INFINITY) continue;  // this lane group has seen no valid row yet
+            if (mnew == -INFINITY) {  // this lane group has seen no row with a score above -inf yet, but perhaps a NaN (which the
+#pragma unroll                          // maximum passes over): the sum keeps it, whatever other rows the group gets to see
+                for (int u = 0; u < DA_U; ++u)
+                    if (sc[gh][u] != sc[gh][u]) den[gh] = sc[gh][u];
+                continue;
+            }
             float alpha = mx[gh] == -INFINITY ? 0.f : __expf(mx[gh] - mnew);
             mx[gh] = mnew;
             den[gh] *= alpha;

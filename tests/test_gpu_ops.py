@@ -1130,3 +1130,39 @@ def test_decode_attention_around_the_sharing_of_items(ops, H, B):
         for u in (0, 1, 2, 3, H - 1):
             ref = orc.attend(qn[b, u], kn[b, u, :n], vn[b, u, :n])
             assert (np.abs(on[b, u] - ref) <= 0.5 * F16_EPS * np.abs(ref) * 1.02 + 2e-5).all(), (b, u)
+
+
+@pytest.mark.parametrize("B,nsplit,H,Hkv", [(1, 1, 4, 4), (3, 2, 4, 4), (72, 1, 32, 32), (2, 1, 8, 2), (72, 1, 32, 8)])
+def test_decode_attention_carries_a_nan_score_and_drops_a_score_of_minus_infinity(ops, B, nsplit, H, Hkv):
+    """A NaN cache row reaches every element of the heads that see it (the saturating half store turns a NaN into the end of the
+    range, 65504 in magnitude), wherever the row falls in the lane groups and wavefronts (alone in its group or not), and nothing
+    else; a key whose score is -inf has weight 0.  Wavefronts share an item, or take one each."""
+    step(f"decode attention, NaN and -inf scores, B={B} nsplit={nsplit} heads={H}/{Hkv}")
+    hd, S, lens, bad = 64, 70, [0, 1, 8, 32, 33, 40, 64, 69], [0, 0, 8, 32, 32, 7, 64, 35]
+    kc, vc = randn_f16((B, Hkv, S, hd), 711), randn_f16((B, Hkv, S, hd), 712)
+    q = randn_f32((B, H, hd), 713).abs()
+    for n, at in zip(lens, bad):
+        d_len = torch.full((B,), n, dtype=torch.int32, device=DEV)
+        for value in (float("nan"), float("-inf")):
+            k = kc.clone()
+            if value != value:
+                k[0, 1, at] = value
+            else:
+                k[0, 1, at] = 0
+                k[0, 1, at, 5] = value
+            out = torch.zeros((B, H * hd), dtype=torch.float16, device=DEV)
+            ws = torch.empty((max(1, ops.decode_attention_ws_floats(B, H, hd, nsplit)),), device=DEV)
+            ops.decode_attention(q, k, vc, d_len, out, ws, B, H, Hkv, hd, S, nsplit, len_stride=1)
+            torch.cuda.synchronize()
+            got = out.reshape(B, Hkv, H // Hkv, hd).float()
+            keep = [j for j in range(n + 1) if j != at]
+            hit = got[0, 1]
+            if value != value or not keep:      # no row is left beside one of weight 0: 0 / 0, as the softmax itself gives
+                assert (torch.isnan(hit) | (hit.abs() == 65504)).all(), (n, at, value)
+            else:
+                for u in range(H // Hkv):
+                    ref = orc.attend(np64(q[0, H // Hkv + u]), np64(kc[0, 1, keep]), np64(vc[0, 1, keep]))
+                    assert (np.abs(np64(hit[u]) - ref) <= 0.5 * F16_EPS * np.abs(ref) * 1.02 + 2e-5).all(), (n, at, u)
+            rest = torch.ones((B, Hkv), dtype=torch.bool, device=DEV)
+            rest[0, 1] = False
+            assert (got[rest].abs() < 10).all(), (n, at, value)
