@@ -1166,3 +1166,86 @@ def test_decode_attention_carries_a_nan_score_and_drops_a_score_of_minus_infinit
             rest = torch.ones((B, Hkv), dtype=torch.bool, device=DEV)
             rest[0, 1] = False
             assert (got[rest].abs() < 10).all(), (n, at, value)
+
+
+# heads, rows and cache layouts of the vector kernel, on both sides of the item counts from which wavefronts no longer share an item
+# (2048, or 512 with several query heads per wavefront)
+@pytest.mark.parametrize("hd,Hq,Hkv,i16,paged,nsplit,Bs", [
+    (128, 32, 32, True, False, 1, (63, 64)), (128, 32, 32, True, True, 1, (63, 64)), (128, 32, 32, False, True, 3, (21, 22)),
+    (64, 32, 32, False, False, 3, (21, 22)), (64, 32, 32, True, True, 3, (21, 22)),
+    (128, 32, 16, True, False, 1, (31, 32)), (128, 32, 16, True, True, 3, (10, 11)), (64, 32, 16, False, True, 1, (31, 32)),
+    (128, 32, 8, True, True, 1, (63, 64)), (128, 32, 8, True, False, 3, (21, 22)), (64, 32, 8, False, False, 1, (63, 64)),
+    (64, 32, 8, False, True, 3, (21, 22))])
+def test_decode_attention_forms_on_both_sides_of_the_sharing_of_items(ops, hd, Hq, Hkv, i16, paged, nsplit, Bs):
+    step(f"decode attention forms hd={hd} heads={Hq}/{Hkv} i16={i16} paged={paged} nsplit={nsplit} B={Bs}")
+    S, page, g = 384, 32, Hq // Hkv
+    # rows of a split: one, below / at / above a trip of 16 or 32 rows, four trips and one more
+    lens = [nsplit * n - 1 for n in (1, 15, 16, 17, 31, 32, 33, 64, 65, 128)]
+    for B in Bs:
+        if i16:
+            (kc, ks, kn), (vc, vs, vn) = (_random_block_scaled((B, Hkv, S, hd), s) for s in (721, 722))
+        else:
+            kc, vc, ks, vs = randn_f16((B, Hkv, S, hd), 721), randn_f16((B, Hkv, S, hd), 722), None, None
+            kn, vn = np64(kc[: len(lens)]), np64(vc[: len(lens)])
+        q = randn_f32((B, Hq * hd), 723, std=0.9)
+        d_len = torch.tensor([lens[b % len(lens)] for b in range(B)], dtype=torch.int32, device=DEV)
+        ws = torch.empty((max(1, ops.decode_attention_ws_floats(B, Hq, hd, nsplit)),), device=DEV)
+        out, lo = (torch.zeros((B, Hq * hd), dtype=torch.float16, device=DEV) for _ in range(2))
+        done = torch.zeros((B,), dtype=torch.int32, device=DEV)
+        done[B - 1] = 1
+        ops.decode_attention(q, kc, vc, d_len, out, ws, B, Hq, Hkv, hd, S, nsplit, len_stride=1, kscale=ks, vscale=vs, out_lo=lo)
+        skip = torch.full_like(out, 7.0)
+        ops.decode_attention(q, kc, vc, d_len, skip, ws, B, Hq, Hkv, hd, S, nsplit, len_stride=1, kscale=ks, vscale=vs, d_done=done)
+        torch.cuda.synchronize()
+        assert torch.equal(skip[: B - 1].view(torch.int16), out[: B - 1].view(torch.int16))
+        if nsplit == 1:   # (with splits the merge rewrites an ended sequence's row from old partials)
+            assert (skip[B - 1] == 7.0).all()
+        if paged:
+            per = S // page
+            order = torch.randperm(B * per, generator=torch.Generator().manual_seed(724)).to(DEV)
+            pool = [None if x is None else torch.empty((B * per, Hkv, page) + x.shape[3:], dtype=x.dtype, device=DEV) for x in (kc, vc, ks, vs)]
+            for x, p in zip((kc, vc, ks, vs), pool):
+                if x is not None:
+                    p[order] = x.unflatten(2, (per, page)).transpose(1, 2).flatten(0, 1)
+            got = torch.zeros_like(out)
+            ops.decode_attention_paged(q, pool[0], pool[1], order.to(torch.int32).reshape(B, per).contiguous(), page, d_len, got, ws, B, Hq,
+                                       Hkv, hd, S, nsplit, len_stride=1, kscale=pool[2], vscale=pool[3])
+            torch.cuda.synchronize()
+            assert torch.equal(got.view(torch.int16), out.view(torch.int16))
+        qn, on, ln = np64(q).reshape(B, Hq, hd), np64(out).reshape(B, Hq, hd), np64(lo).reshape(B, Hq, hd)
+        for b in range(min(B, len(lens))):
+            for u in (0, 1, g, Hq - 1):
+                ref = orc.attend(qn[b, u], kn[b, u // g, : lens[b] + 1], vn[b, u // g, : lens[b] + 1])
+                assert (np.abs(on[b, u] - ref) <= 0.5 * F16_EPS * np.abs(ref) * 1.02 + 2e-5).all(), (B, b, u)
+                assert (np.abs(on[b, u] + ln[b, u] - ref) <= 2e-5 * (1 + np.abs(ref))).all(), (B, b, u)
+
+
+@pytest.mark.parametrize("hd,Hq,Hkv,nsplit,Bs", [(128, 32, 32, 1, (63, 64)), (64, 32, 16, 3, (10, 11)), (64, 32, 8, 1, (63, 64))])
+def test_fused_decode_attention_on_both_sides_of_the_sharing_of_items(ops, hd, Hq, Hkv, nsplit, Bs):
+    step(f"fused decode attention hd={hd} heads={Hq}/{Hkv} nsplit={nsplit} B={Bs}")
+    S, nq, g, ld = 384, 2, Hq // Hkv, (Hq + 2 * Hkv) * hd
+    tab = torch.empty((S, hd // 2, 2), dtype=torch.float32, device=DEV)
+    ops.build_rope_table(tab, S, hd, 10000.0)
+    lens = [0, 15, 16, 32, 63, 64, 159]
+    for B in Bs:
+        qkv = randn_f32((nq, B, ld), 731, std=0.8)
+        kc, vc = randn_f16((B, Hkv, S, hd), 732), randn_f16((B, Hkv, S, hd), 733)
+        for b in range(B):
+            kc[b, :, lens[b % len(lens)]:] = float("nan")
+            vc[b, :, lens[b % len(lens)]:] = float("nan")
+        d_len = torch.tensor([lens[b % len(lens)] for b in range(B)], dtype=torch.int32, device=DEV)
+        out = torch.zeros((B, Hq * hd), dtype=torch.float16, device=DEV)
+        ws = torch.empty((max(1, ops.decode_attention_ws_floats(B, Hq, hd, nsplit)),), device=DEV)
+        ops.decode_attention_fused(qkv, nq, B * ld, tab, 1, kc, vc, d_len, out, ws, B, Hq, Hkv, hd, S, nsplit, len_stride=1)
+        torch.cuda.synchronize()
+        tot, on = np64(qkv).sum(0), np64(out).reshape(B, Hq, hd)
+        for b in range(len(lens)):
+            n = lens[b]
+            q = orc.rope(tot[b, : Hq * hd].reshape(Hq, hd), n, 10000.0, 1)
+            k = orc.rope(tot[b, Hq * hd: (Hq + Hkv) * hd].reshape(Hkv, hd), n, 10000.0, 1)
+            kn, vn = np64(kc[b]), np64(vc[b])
+            assert (np.abs(kn[:, n] - k) <= 0.5 * F16_EPS * np.abs(k) * 1.01 + 1e-6).all()
+            assert np.isnan(kn[:, n + 1:]).all()
+            for u in (0, 1, g, Hq - 1):
+                ref = orc.attend(q[u], kn[u // g, : n + 1], vn[u // g, : n + 1])
+                assert (np.abs(on[b, u] - ref) <= 0.5 * F16_EPS * np.abs(ref) * 1.02 + 3e-5).all(), (B, b, u)
