@@ -4,7 +4,8 @@
 // loading the irreducible overhead of generation), so this kernel is a pure HBM stream: each cache
 // element is used once per query head that shares it.  Design for gfx950:
 //   * one WAVEFRONT per (sequence, kv head, group of GT query heads, sequence split); no LDS and no
-//     barriers on the streaming path;
+//     barriers on the streaming path.  Where that leaves the chip idle (small batches) the four wavefronts of a
+//     workgroup share one such item: they take its rows in turn and meet once, at the end, in LDS;
 //   * the cache slab of one (sequence, kv head) is contiguous [position][head_dim], so a wavefront
 //     load instruction fetches 1 KB of consecutive bytes (64 lanes x 16 B = 4 rows of head_dim 128);
 //   * a lane owns 8 consecutive head_dim elements; q.k is finished by a 16-lane DPP reduction;
@@ -94,8 +95,11 @@ __device__ __forceinline__ void rotate8(float x[8], int c, const float *tab /* r
 // out_lo (optional): second half term of the output, half(o - half(o)), for a two-term output projection.
 // WS: wavefronts that share an item (1, or the four of a workgroup).  Shared, they take its trips of cache rows in turn and the
 // first one merges their four partial results through LDS.
+// (Two heads per wavefront over contiguous block-scaled rows of head_dim 128 need 128 registers, the most that four wavefronts per SIMD
+// can have; left alone the compiler takes 131 and one wavefront fewer fits.)
+#define DA_MIN_WAVES (HD == 128 && GT == 2 && I16 && !PAGED ? 4 : 1)
 template <int HD, int GT, bool FUSED, bool PAGED, bool I16, int WS>
-__global__ __launch_bounds__(DA_THREADS) void decode_attention_kernel(
+__global__ __launch_bounds__(DA_THREADS, DA_MIN_WAVES) void decode_attention_kernel(
     const float *__restrict__ q, f16_t *kc, f16_t *vc, const int32_t *__restrict__ d_len, f16_t *__restrict__ out,
     f16_t *__restrict__ out_lo, float *__restrict__ ws, int n_items, int Hq, int Hkv, int S, int nsplit, int len_stride,
     FusedQkv fq, KvMap map, const int32_t *__restrict__ d_done) {
@@ -104,7 +108,7 @@ __global__ __launch_bounds__(DA_THREADS) void decode_attention_kernel(
     constexpr int LPR = HD / 8;     // lanes per cache row
     constexpr int RPW = 64 / LPR;   // rows per wavefront load instruction
     const int lane = threadIdx.x & 63;
-    const int item = blockIdx.x * (DA_THREADS / 64 / WS) + (threadIdx.x >> 6) / WS;
+    const int item = WS == 4 ? blockIdx.x : blockIdx.x * (DA_THREADS / 64) + (threadIdx.x >> 6);
     const int wi = WS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // this wavefront's turn
     if (item >= n_items) return;
     const int g = Hq / Hkv, hgs = g / GT;
@@ -123,6 +127,10 @@ __global__ __launch_bounds__(DA_THREADS) void decode_attention_kernel(
     const int chunk = (n + nsplit - 1) / nsplit;
     const int j0 = split * chunk;
     const int j1 = j0 + chunk < n ? j0 + chunk : n;
+
+    // a single trip: nothing to share, the first wavefront does it alone (the same for the whole workgroup)
+    const bool alone = WS > 1 && j1 - j0 <= RPW * DA_U;
+    if (alone && wi != 0) return;
 
     const int c = lane % LPR, r = lane / LPR;
     float qr[GT][8];
@@ -276,9 +284,10 @@ __global__ __launch_bounds__(DA_THREADS) void decode_attention_kernel(
 #pragma unroll
             for (int u = 0; u < DA_U; ++u) mnew = fmaxf(mnew, sc[gh][u]);
             if (mnew == -INFINITY) {  // this lane group has seen no row with a score above -inf yet, but perhaps a NaN (which the
-#pragma unroll                          // maximum passes over): the sum keeps it, whatever other rows the group gets to see
-                for (int u = 0; u < DA_U; ++u)
-                    if (sc[gh][u] != sc[gh][u]) den[gh] = sc[gh][u];
+                float s = sc[gh][0];  // maximum passes over): the sum keeps it, whatever other rows the group gets to see
+#pragma unroll
+                for (int u = 1; u < DA_U; ++u) s += sc[gh][u];
+                if (s != s) den[gh] = s;
                 continue;
             }
             float alpha = mx[gh] == -INFINITY ? 0.f : __expf(mx[gh] - mnew);
@@ -296,6 +305,35 @@ __global__ __launch_bounds__(DA_THREADS) void decode_attention_kernel(
             }
         }
     }
+
+    // the finished (or, with splits, partial) result of one head: maximum m, sum l and weighted values in acc[gh]
+    auto store = [&](int gh, float m, float l) {
+        if (r != 0) return;
+        int head = head0 + gh;
+        if (nsplit == 1) {
+            float inv = 1.0f / l;
+            u32x4_t o4;
+            o4.x = pack_f16x2(acc[gh][0] * inv, acc[gh][1] * inv);
+            o4.y = pack_f16x2(acc[gh][2] * inv, acc[gh][3] * inv);
+            o4.z = pack_f16x2(acc[gh][4] * inv, acc[gh][5] * inv);
+            o4.w = pack_f16x2(acc[gh][6] * inv, acc[gh][7] * inv);
+            *reinterpret_cast<u32x4_t *>(out + ((size_t)b * Hq + head) * HD + c * 8) = o4;
+            if (out_lo) {
+                u32x4_t l4;
+                l4.x = pack_f16x2_lo(acc[gh][0] * inv, acc[gh][1] * inv, o4.x);
+                l4.y = pack_f16x2_lo(acc[gh][2] * inv, acc[gh][3] * inv, o4.y);
+                l4.z = pack_f16x2_lo(acc[gh][4] * inv, acc[gh][5] * inv, o4.z);
+                l4.w = pack_f16x2_lo(acc[gh][6] * inv, acc[gh][7] * inv, o4.w);
+                *reinterpret_cast<u32x4_t *>(out_lo + ((size_t)b * Hq + head) * HD + c * 8) = l4;
+            }
+        } else {
+            float *p = ws + (((size_t)b * Hq + head) * nsplit + split) * (HD + 2);
+            if (c == 0) { p[0] = m; p[1] = l; }
+            float *ps = p + 2 + c * 8;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ps[i] = acc[gh][i];
+        }
+    };
 
     // ---- merge the RPW lane groups (lanes with equal c) of the wavefront
     __shared__ float share[WS == 1 ? 1 : WS * GT * (HD + 2)];
@@ -316,23 +354,28 @@ __global__ __launch_bounds__(DA_THREADS) void decode_attention_kernel(
             for (int o = LPR; o < 64; o <<= 1) a += __shfl_xor(a, o, 64);
             acc[gh][i] = a;
         }
+        if (WS == 1) {
+            store(gh, m, l);
+            continue;
+        }
         ml[gh] = m;
         ll[gh] = l;
-        if (WS > 1 && r == 0) {
+        if (!alone && r == 0) {
             float *sp = share + (wi * GT + gh) * (HD + 2);
             if (c == 0) { sp[HD] = m; sp[HD + 1] = l; }
 #pragma unroll
             for (int i = 0; i < 8; ++i) sp[c * 8 + i] = acc[gh][i];
         }
     }
-    if (WS > 1) {
+    if (WS == 1) return;
+    if (!alone) {
         __syncthreads();
         if (wi != 0) return;
     }
 #pragma unroll
     for (int gh = 0; gh < GT; ++gh) {
         float m = ml[gh], l = ll[gh];
-        if (WS > 1) {  // partials of the sharing wavefronts, in their order
+        if (!alone) {  // partials of the sharing wavefronts, in their order
 #pragma unroll
             for (int w = 1; w < WS; ++w) m = fmaxf(m, share[(w * GT + gh) * (HD + 2) + HD]);
             float wgt = ml[gh] == -INFINITY ? 0.f : __expf(ml[gh] - m);
@@ -349,32 +392,7 @@ __global__ __launch_bounds__(DA_THREADS) void decode_attention_kernel(
                 for (int i = 0; i < 8; ++i) acc[gh][i] = fmaf(sp[c * 8 + i], wgt, acc[gh][i]);
             }
         }
-        if (r == 0) {
-            int head = head0 + gh;
-            if (nsplit == 1) {
-                float inv = 1.0f / l;
-                u32x4_t o4;
-                o4.x = pack_f16x2(acc[gh][0] * inv, acc[gh][1] * inv);
-                o4.y = pack_f16x2(acc[gh][2] * inv, acc[gh][3] * inv);
-                o4.z = pack_f16x2(acc[gh][4] * inv, acc[gh][5] * inv);
-                o4.w = pack_f16x2(acc[gh][6] * inv, acc[gh][7] * inv);
-                *reinterpret_cast<u32x4_t *>(out + ((size_t)b * Hq + head) * HD + c * 8) = o4;
-                if (out_lo) {
-                    u32x4_t l4;
-                    l4.x = pack_f16x2_lo(acc[gh][0] * inv, acc[gh][1] * inv, o4.x);
-                    l4.y = pack_f16x2_lo(acc[gh][2] * inv, acc[gh][3] * inv, o4.y);
-                    l4.z = pack_f16x2_lo(acc[gh][4] * inv, acc[gh][5] * inv, o4.z);
-                    l4.w = pack_f16x2_lo(acc[gh][6] * inv, acc[gh][7] * inv, o4.w);
-                    *reinterpret_cast<u32x4_t *>(out_lo + ((size_t)b * Hq + head) * HD + c * 8) = l4;
-                }
-            } else {
-                float *p = ws + (((size_t)b * Hq + head) * nsplit + split) * (HD + 2);
-                if (c == 0) { p[0] = m; p[1] = l; }
-                float *ps = p + 2 + c * 8;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) ps[i] = acc[gh][i];
-            }
-        }
+        store(gh, m, l);
     }
 }
 
@@ -420,14 +438,19 @@ int decode_attention_default_splits(int B, int Hkv, int S) {
 
 // Few items: the four wavefronts of a workgroup share one, so that a sequence's rows are requested four trips at a time instead
 // of one after the other (what bounds a small batch is the latency of that chain; a further split over workgroups would need
-// the merge launch).  32 heads, block-scaled rows, batch 1, 128 rows: 13.5 -> 9.3 us including the launch; batch 16 15.6 -> 10.8;
-// batch 24, 2048 rows in 3 splits 139 -> 132.  From 2048 items (two wavefronts per SIMD) on the gain turns with the length (batch 64:
-// 384 rows 61.6 -> 66.8, 1024 rows 172 -> 164), and with several query heads per wavefront (more registers, more to merge) it
-// ends at 512 items (64/8 heads: 384 items 16.9 -> 15.2, 768 items 17.1 -> 20.9).
-// The order of a sequence's sums depends on it, so a generator decides once, for its capacity: a batch that shrinks keeps its bits.
-bool decode_attention_shares_items(int B, int Hq, int Hkv, int nsplit) {
+// the merge launch).  32 heads, block-scaled rows, one split, us per launch at 16 / 64 / 255 rows, one wavefront -> four: batch 1
+// 3.3 / 5.2 / 22.5 -> 3.0 / 3.5 / 8.9; batch 32 5.6 / 12.0 / 34.4 -> 5.5 / 8.5 / 24.3; batch 63 7.4 / 17.6 / 51.8 -> 7.9 / 13.4 /
+// 43.6.  From 2048 items (two wavefronts per SIMD) on the gain turns with the length (batch 64: 384 rows 61.6 -> 66.8, 1024 rows
+// 172 -> 164), and with several query heads per wavefront (more registers, more to merge) it ends at 512 items (64/8 heads:
+// 384 items 16.9 -> 15.2, 768 items 17.1 -> 20.9).  Over the upper half of either range the first rows of a cache are slower shared
+// (three idle wavefronts to start per item: 2016 items 4 rows 4.5 -> 5.7, 17 rows 8.9 -> 9.4; 504 items of 32/8 heads 5.8 -> 6.2,
+// 8.7 -> 9.1; gains from 33 rows on), so there only a split that grows to 128 rows is shared.
+// The order of a sequence's sums depends on the choice, so a generator makes it once, for its capacity: a batch that shrinks keeps
+// its bits.
+bool decode_attention_shares_items(int B, int Hq, int Hkv, int S, int nsplit) {
     const int g = Hq / Hkv, gt = decode_attention_group(g);
-    return (long)B * Hkv * (g / gt) * nsplit < (gt == 1 ? 2048 : 512);
+    const long items = (long)B * Hkv * (g / gt) * nsplit, limit = gt == 1 ? 2048 : 512;
+    return items < limit / 2 || (items < limit && S / nsplit >= 128);
 }
 
 template <int HD, int GT, int WS>
@@ -486,7 +509,7 @@ void launch_decode_attention_fused(const float *qkv, int nsplit_qkv, size_t spli
     FusedQkv fq;
     fq.part = qkv; fq.nsplit = nsplit_qkv; fq.split_stride = split_stride; fq.rope_tab = rope_tab; fq.rope_style = rope_style;
     dispatch_da(nullptr, kc, vc, d_len, len_stride, out, nullptr, ws, B, Hq, Hkv, hd, S, nsplit,
-                decode_attention_shares_items(B, Hq, Hkv, nsplit), &fq, KvMap(), nullptr, st);
+                decode_attention_shares_items(B, Hq, Hkv, S, nsplit), &fq, KvMap(), nullptr, st);
 }
 
 void launch_decode_attention_merge(const float *ws, f16_t *out, int B, int Hq, int hd, int nsplit, hipStream_t st, f16_t *out_lo) {

@@ -176,7 +176,7 @@ void launch_decode_attention_merge(const float *ws, f16_t *out, int B, int Hq, i
 size_t decode_attention_ws_floats(int B, int Hq, int hd, int nsplit);
 int decode_attention_default_splits(int B, int Hkv, int S);
 int decode_attention_group(int g);  // query heads per wavefront for Hq/Hkv = g
-bool decode_attention_shares_items(int B, int Hq, int Hkv, int nsplit);
+bool decode_attention_shares_items(int B, int Hq, int Hkv, int S, int nsplit);
 
 // ---- attention_prefill.hip -----------------------------------------------------------------------
 // Causal attention over the T prompt positions of nb sequences whose K/V already sit in the cache.

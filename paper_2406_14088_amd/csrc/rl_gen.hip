@@ -790,7 +790,7 @@ static int create_impl(const rl_gen_shape *shape, const rl_gen_weights *w, void 
     h->work = reinterpret_cast<unsigned char *>(work_arena);
     h->wp = wp;
     h->nsplit_attn = attn_splits(shape);
-    h->share_attn = decode_attention_shares_items(shape->max_batch, shape->n_heads, shape->n_kv_heads, h->nsplit_attn);
+    h->share_attn = decode_attention_shares_items(shape->max_batch, shape->n_heads, shape->n_kv_heads, shape->max_seq, h->nsplit_attn);
     h->prec = prec_level(shape);
     h->kv_i16 = kv_block_scaled(shape);
     h->B = 0; h->len = 0;
@@ -1587,7 +1587,7 @@ int rl_op_decode_attention(const float *q, const uint16_t *kc, const uint16_t *v
     KvMap map;
     map.kscale = const_cast<float *>(kscale); map.vscale = const_cast<float *>(vscale);
     launch_decode_attention(q, kc, vc, d_len, len_stride, out, ws, B, Hq, Hkv, hd, S, nsplit,
-                            decode_attention_shares_items(B, Hq, Hkv, nsplit), reinterpret_cast<hipStream_t>(st), map, d_done, out_lo);
+                            decode_attention_shares_items(B, Hq, Hkv, S, nsplit), reinterpret_cast<hipStream_t>(st), map, d_done, out_lo);
     RL_OP_RETURN();
 }
 
@@ -1613,7 +1613,7 @@ int rl_op_decode_attention_noalloc(const float *q, const uint16_t *kc, const uin
     KvMap map;
     map.kscale = const_cast<float *>(kscale); map.vscale = const_cast<float *>(vscale);
     launch_decode_attention(q, kc, vc, d_len, len_stride, out, reinterpret_cast<float *>(ws), B, Hq, Hkv, hd, S, nsplit,
-                            decode_attention_shares_items(B, Hq, Hkv, nsplit), reinterpret_cast<hipStream_t>(st), map, d_done, out_lo);
+                            decode_attention_shares_items(B, Hq, Hkv, S, nsplit), reinterpret_cast<hipStream_t>(st), map, d_done, out_lo);
     RL_OP_RETURN();
 }
 
@@ -1631,7 +1631,7 @@ int rl_op_decode_attention_paged(const float *q, const uint16_t *k_pool, const u
     map.table = table; map.table_stride = table_stride; map.page_shift = shift;
     map.kscale = const_cast<float *>(kscale); map.vscale = const_cast<float *>(vscale);
     launch_decode_attention(q, k_pool, v_pool, d_len, len_stride, out, ws, B, Hq, Hkv, hd, S, nsplit,
-                            decode_attention_shares_items(B, Hq, Hkv, nsplit), reinterpret_cast<hipStream_t>(st), map);
+                            decode_attention_shares_items(B, Hq, Hkv, S, nsplit), reinterpret_cast<hipStream_t>(st), map);
     RL_OP_RETURN();
 }
 

@@ -1249,3 +1249,24 @@ def test_fused_decode_attention_on_both_sides_of_the_sharing_of_items(ops, hd, H
             for u in (0, 1, g, Hq - 1):
                 ref = orc.attend(q[u], kn[u // g, : n + 1], vn[u // g, : n + 1])
                 assert (np.abs(on[b, u] - ref) <= 0.5 * F16_EPS * np.abs(ref) * 1.02 + 3e-5).all(), (B, b, u)
+
+
+@pytest.mark.parametrize("hd,Hq,Hkv,S,Bs", [(128, 32, 32, 384, (63, 64)), (64, 32, 16, 384, (31, 32)), (128, 32, 32, 100, (31, 32)),
+                                            (64, 32, 8, 100, (31, 32))])
+def test_decode_attention_of_one_trip_is_the_same_shared_or_not(ops, hd, Hq, Hkv, S, Bs):
+    """Rows that fit the first trip (16 of head_dim 128, 32 of 64) are one wavefront's work either way: the same bits on both sides of
+    the limit, which lies at half the items where a split cannot reach 128 rows.  One row more only has to be the same to rounding."""
+    trip = 2048 // hd
+    lens = [0, 1, trip // 2, trip - 2, trip - 1, trip]
+    outs = []
+    for B in Bs:
+        kc, vc = randn_f16((Bs[1], Hkv, S, hd), 741)[:B].contiguous(), randn_f16((Bs[1], Hkv, S, hd), 742)[:B].contiguous()
+        q = randn_f32((Bs[1], Hq * hd), 743)[:B].contiguous()
+        d_len = torch.tensor([lens[b % len(lens)] for b in range(B)], dtype=torch.int32, device=DEV)
+        out = torch.zeros((B, Hq * hd), dtype=torch.float16, device=DEV)
+        ops.decode_attention(q, kc, vc, d_len, out, torch.empty(1, device=DEV), B, Hq, Hkv, hd, S, 1, len_stride=1)
+        torch.cuda.synchronize()
+        outs.append(out[: len(lens)])
+    a, b = outs
+    assert torch.equal(a[:-1].view(torch.int16), b[:-1].view(torch.int16)) and a.abs().min() >= 0 and torch.isfinite(a).all()
+    assert ((a[-1].float() - b[-1].float()).abs() <= F16_EPS * a[-1].float().abs() + 2e-5).all()
