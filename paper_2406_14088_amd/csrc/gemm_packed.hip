@@ -514,7 +514,7 @@ static void launch_p2(PackedParams &p, hipStream_t st) {
     p.zblocks = ceil_div(p.M, BM);
     p.group_z = p.splits == 1 && p.zblocks >= 2 * PK_GROUP_Z ? 1 : 0;
     int ids = p.group_z ? ceil_div(p.tiles * p.zblocks, 8) * 8 : ceil_div(p.tiles * p.splits, 8) * 8 * p.zblocks;
-    if constexpr (NB == 2 && MT == 4 && RC == 2 && !SW) {
+    if constexpr (((NB == 2 && MT == 4) || (NB == 1 && MT == 2)) && RC == 2 && !SW) {
         if (p.epilogue == EPI_ROPE) {
             static bool rope_attr_set = false;
             if (!rope_attr_set) {

@@ -135,7 +135,7 @@ struct PackedGemmArgs {
     float *cand_val = nullptr;
     int32_t *cand_idx = nullptr;
     bool no_store = false;
-    const RopeEpilogue *rope = nullptr;  // EPI_ROPE (gemm_packed_rope_supported): nb = 2, rows_per_wg = 128, depth = 2
+    const RopeEpilogue *rope = nullptr;  // EPI_ROPE (gemm_packed_rope_supported): nb 2 and 128 rows per workgroup, or 1 and 64; depth 2
 };
 bool gemm_packed_rope_supported(int M, int K, int64_t lda, int Hq, int hd, int rope_style);
 bool gemm_packed_single_launch(int N, int K);  // the matrix is served by one launch (no row slabs): candidates are possible

@@ -1066,11 +1066,12 @@ def test_qkv_projection_with_rotary_epilogue_block_scaled_equals_the_two_kernels
 
 
 @pytest.mark.parametrize("Hq,Hkv,T,nseq,two,bs,page", [(2, 2, 40, 4, True, True, 0), (3, 1, 7, 37, False, False, 0), (8, 2, 33, 34, True, False, 16),
-                                                       (1, 1, 300, 1, True, True, 64)])
+                                                       (1, 1, 300, 1, True, True, 64), (5, 3, 65, 2, True, True, 0), (9, 3, 119, 15, True, True, 0),
+                                                       (9, 3, 113, 17, False, False, 16), (8, 8, 131, 10, True, False, 0)])
 def test_gemm_packed_rope_equals_projection_then_rope_append(ops, Hq, Hkv, T, nseq, two, bs, page):
     """The fused epilogue stores the bits that the packed projection (fp32) followed by rope_append stores: prompts shorter and
     longer than a row block, odd head counts (a last column tile of one head), paged pools; rows beyond a sequence's own
-    length stay out of the cache."""
+    length stay out of the cache.  126 tiles of 128 rows x 2 heads and fewer run as tiles of 64 rows x 1 head; 132 and 144 as they are."""
     step(f"packed rope heads={Hq}/{Hkv} T={T} nseq={nseq} two={two} bs={bs} page={page}")
     hd, K, b0, S = 128, 200, 1, T + 9
     M, n_all = nseq * T, (Hq + 2 * Hkv) * hd
