@@ -497,6 +497,16 @@ __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_pa
     }
 }
 
+// Where the grouped tile order pays (row blocks of 128, us before -> after).  From 16 row blocks on for the shared operands: 7B shape
+// 4096 rows gate/up 677 -> 636, 2048 rows 350 -> 345; hidden 1024 6400 rows down 143 -> 94.  With 8 to 15 the sharing is worth less than
+// what the plain order's one column tile per XCD at a time gives (7B 900-1792 rows O 115 -> 120, down 273 -> 281; 70B shape 1152 rows
+// down 1254 -> 1303) unless the plain order, which hands out whole column tiles, puts one workgroup more on the compute units of
+// some XCDs than an even share would: 20 column tiles x 11 row blocks, 33 against 28 workgroups on an XCD of 32: 540 -> 387.
+static bool grouped_tile_order(int tiles, int zblocks) {
+    const int plain = ceil_div(ceil_div(tiles, 8) * zblocks, 32), even = ceil_div(ceil_div(tiles * zblocks, 8), 32);
+    return zblocks >= 4 * PK_GROUP_Z || (zblocks >= 2 * PK_GROUP_Z && even < plain);
+}
+
 template <int NB, int TERMS, int MT, int RC, bool SW>
 static void launch_p2(PackedParams &p, hipStream_t st) {
     constexpr int NBUF = TERMS == 1 ? 3 : 2;
@@ -512,7 +522,7 @@ static void launch_p2(PackedParams &p, hipStream_t st) {
         attr_set = true;
     }
     p.zblocks = ceil_div(p.M, BM);
-    p.group_z = p.splits == 1 && p.zblocks >= 2 * PK_GROUP_Z ? 1 : 0;
+    p.group_z = p.splits == 1 && grouped_tile_order(p.tiles, p.zblocks) ? 1 : 0;
     int ids = p.group_z ? ceil_div(p.tiles * p.zblocks, 8) * 8 : ceil_div(p.tiles * p.splits, 8) * 8 * p.zblocks;
     if constexpr (((NB == 2 && MT == 4) || (NB == 1 && MT == 2)) && RC == 2 && !SW) {
         if (p.epilogue == EPI_ROPE) {

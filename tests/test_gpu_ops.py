@@ -267,10 +267,13 @@ def test_gemm_packed_f32(ops, M, K, rows, splits, nb, terms, rpw):
     assert np.abs(got - ref).max() <= tol, (np.abs(got - ref).max(), tol)
 
 
-# row blocks of 128 (or 32): one below, at and above the count from which tiles are walked in groups of row blocks; tile counts that
-# do not divide by the 8 XCDs, a last group of fewer row blocks
+# row blocks of 128 (or 32): below, at and above the counts from which tiles are walked in groups of row blocks (16; 8 where whole
+# column tiles would load some of the 8 XCDs more: 17 column tiles x 11 row blocks); tile counts that do not divide by 8, a last
+# group of fewer row blocks
 @pytest.mark.parametrize("M,K,rows,nb,terms,rpw", [(7 * 128, 136, (300,), 2, 2, 128), (8 * 128, 72, (1000, 72, 40), 1, 1, 128),
-                                                   (9 * 128 + 70, 136, (1400,), 2, 2, 128), (33 * 32 + 1, 200, (260,), 1, 2, 32)])
+                                                   (9 * 128 + 70, 136, (1400,), 2, 2, 128), (33 * 32 + 1, 200, (260,), 1, 2, 32),
+                                                   (15 * 128, 72, (300,), 2, 1, 128), (16 * 128, 72, (1000, 72, 40), 1, 1, 128),
+                                                   (17 * 128 + 70, 136, (700,), 2, 2, 128), (11 * 128 - 3, 72, (2100,), 1, 2, 128)])
 def test_gemm_packed_many_row_blocks(ops, M, K, rows, nb, terms, rpw):
     step(f"gemm_packed many row blocks M={M} K={K} rows={rows} nb={nb} terms={terms} rows_per_wg={rpw}")
     A = randn_f16((M, K), 220 + M)
