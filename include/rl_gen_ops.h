@@ -127,7 +127,7 @@ int rl_op_lm_head_argmax(const uint16_t *A, const uint16_t *A_lo, int64_t lda, c
 /* Fused gate/up projection of few rows from fragment-order copies, the two 64-wide halves of every 128-wide K chunk on
  * separate wavefronts: out[M, F] (DEVICE half, row stride ldc) = silu(A Pg^T) * (A Pu^T), A DEVICE half [M, K] with row stride lda,
  * Pg and Pu = rl_op_pack_weights of the gate and up matrices [F, K].  The sums are formed in the order of rl_op_gemm's kernel 1 with
- * epilogue 1, so the two calls store the same bits.  depth: 128-wide weight chunks in flight per wavefront, 2 or 4 (0: 4).
+ * epilogue 1, so the two calls store the same bits.  depth: 0, 2 or 4, without effect (two weight chunks are in flight).
  * K % 8 == 0, lda % 8 == 0, each packed matrix below 3.75 GB; RL_GEN_E_SHAPE otherwise. */
 int rl_op_gemm_packed_swiglu_halves(const uint16_t *A, int64_t lda, const uint16_t *Pg, const uint16_t *Pu, int32_t F, int32_t M,
                                     int32_t K, uint16_t *out, int64_t ldc, int32_t depth, uint16_t *out_lo, void *hip_stream);

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_pa
     if (p.group_z) {
         const int total = p.tiles * p.zblocks;
         const int at = (id & 7) * ((total + 7) >> 3) + (id >> 3);
-        if ((id >> 3) >= ((total + 7) >> 3) || at >= total) return;  // padding of the id space (whole workgroup, before any barrier)
+        if (at >= total) return;  // padding of the id space (whole workgroup, before any barrier)
         const int group = at / (PK_GROUP_Z * p.tiles);
         const int in = at - group * PK_GROUP_Z * p.tiles;
         const int gz = p.zblocks - group * PK_GROUP_Z < PK_GROUP_Z ? p.zblocks - group * PK_GROUP_Z : PK_GROUP_Z;
@@ -586,12 +586,14 @@ static void launch_pm(PackedParams &p, int mt, int depth, hipStream_t st) {
 // global -> LDS by the load unit and each half is read by two wavefronts: 96 KB per chunk.  At the end the kg = 1
 // wavefronts hand their sums to kg = 0 through LDS, which applies the SwiGLU.  The order of every sum -- the K half of
 // each chunk in ascending chunks, then half 0 + half 1 -- is that of the row-major kernel, and so are the results, bit for
-// bit.  One workgroup per compute unit (the register ring holds RC chunks of weight fragments: 8 KB each).
+// bit.  One workgroup per compute unit (the register ring holds two chunks of weight fragments, 8 KB each; with four the time was 1-2 %
+// longer from 1 to 512 rows of FFN 5504 to 14336 and 13 % longer at FFN 688).
 #define PS_BK 128
-template <int MT, int RC, bool SW>
+template <int MT, bool SW>
 __global__ __launch_bounds__(PK_THREADS, 1) void gemm_packed_swiglu_halves_kernel(PackedParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int BM = 32 * MT, NBUF = 3;
+    constexpr int RC = 2;                // chunks of weight fragments in flight
     constexpr int XTILE = BM * 64 * 2;   // one 64-wide half of an activation chunk
     constexpr int XBUF = 2 * XTILE;
     const int t = threadIdx.x, lane = t & 63;
@@ -616,7 +618,7 @@ __global__ __launch_bounds__(PK_THREADS, 1) void gemm_packed_swiglu_halves_kerne
     const uint32_t w_off = ((uint32_t)nb * (uint32_t)p.ksteps * 64u + (uint32_t)lane) * 16u;
     const int trips = (K + PS_BK - 1) / PS_BK;
 
-    // activation copy: instruction i of wavefront w fills rows 8 (4 w + i) .. + 7 of one half; piece g of row r sits in
+    // activation copy: instruction i of wavefront w fills rows 8 (MT w + i) .. + 7 of one half; piece g of row r sits in
     // slot g ^ ((r >> 1) & 7), as in gemm_packed_kernel
     __amdgpu_buffer_rsrc_t ar = pk_rsrc(p.A, p.a_bytes);
     uint32_t x_off[MT];
@@ -707,14 +709,8 @@ __global__ __launch_bounds__(PK_THREADS, 1) void gemm_packed_swiglu_halves_kerne
         for (int c = 0; c < trips; c += RC) {  // trips past the end multiply zero tiles
             body(c, buf, std::integral_constant<int, 0>{});
             buf = buf + 1 == NBUF ? 0 : buf + 1;
-            body(c + 1, buf, std::integral_constant<int, 1 % RC>{});
+            body(c + 1, buf, std::integral_constant<int, 1>{});
             buf = buf + 1 == NBUF ? 0 : buf + 1;
-            if constexpr (RC == 4) {
-                body(c + 2, buf, std::integral_constant<int, 2 % RC>{});
-                buf = buf + 1 == NBUF ? 0 : buf + 1;
-                body(c + 3, buf, std::integral_constant<int, 3 % RC>{});
-                buf = buf + 1 == NBUF ? 0 : buf + 1;
-            }
         }
     }
     __builtin_amdgcn_s_waitcnt(0);  // copies issued for chunks past the end (zeros) must have landed before the memory is reused
@@ -776,19 +772,19 @@ __global__ __launch_bounds__(PK_THREADS, 1) void gemm_packed_swiglu_halves_kerne
     }
 }
 
-template <int MT, int RC, bool SW>
+template <int MT, bool SW>
 static void launch_halves(PackedParams &p, hipStream_t st) {
     size_t lds = (size_t)3 * 2 * 32 * MT * 64 * 2;  // three chunk buffers
     const size_t epi = (size_t)2 * 2 * MT * 16 * 64 * 4 + (size_t)2 * 32 * MT * 72 * 2;  // exchange area + both output tiles
     if (epi > lds) lds = epi;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_packed_swiglu_halves_kernel<MT, RC, SW>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_packed_swiglu_halves_kernel<MT, SW>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         attr_set = true;
     }
     int ids = ceil_div(p.tiles, 8) * 8 * p.zblocks;
-    gemm_packed_swiglu_halves_kernel<MT, RC, SW><<<ids, PK_THREADS, lds, st>>>(p);
+    gemm_packed_swiglu_halves_kernel<MT, SW><<<ids, PK_THREADS, lds, st>>>(p);
 }
 
 bool gemm_packed_swiglu_halves_supported(int F, int K) {
@@ -816,11 +812,10 @@ void launch_gemm_packed_swiglu_halves(const PackedGemmArgs &a, hipStream_t st) {
     p.tiles = ceil_div(a.rows[0], 64);
     p.zblocks = ceil_div(a.M, 128);
     if (p.tiles <= 0) return;
-    const bool deep = a.depth != 2;
-    if (a.M <= 32) { if (deep) launch_halves<1, 4, true>(p, st); else launch_halves<1, 2, true>(p, st); }
-    else if (a.M <= 64) { if (deep) launch_halves<2, 4, true>(p, st); else launch_halves<2, 2, true>(p, st); }
-    else if (p.zblocks == 1) { if (deep) launch_halves<4, 4, true>(p, st); else launch_halves<4, 2, true>(p, st); }
-    else { if (deep) launch_halves<4, 4, false>(p, st); else launch_halves<4, 2, false>(p, st); }
+    if (a.M <= 32) launch_halves<1, true>(p, st);
+    else if (a.M <= 64) launch_halves<2, true>(p, st);
+    else if (p.zblocks == 1) launch_halves<4, true>(p, st);
+    else launch_halves<4, false>(p, st);  // several row blocks: the single-operation entry point only
 }
 
 // Decomposition of a projection with fp32 partial outputs.  Measured inside whole decode steps of the 7B shape,

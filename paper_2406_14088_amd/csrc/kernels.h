@@ -66,9 +66,9 @@ enum GemmEpilogue {
     EPI_F32 = 0,    // out fp32: split s writes out + s*split_stride, element [m*ldc + col]
     EPI_SWIGLU = 1, // W_0 = gate, W_1 = up (same shape): out half [m*ldc + n] = silu(gate) * up; splits must be 1
     EPI_F32_ACC = 2, // out fp32 [m*ldc + col] += result (residual add); splits must be 1
-    EPI_ROPE = 3,    // tiled kernel only: W_0, W_1, W_2 = Wq, Wk, Wv; the result is rotated and stored as launch_rope_append
+    EPI_ROPE = 3,    // tiled and packed kernels: W_0, W_1, W_2 = Wq, Wk, Wv; the result is rotated and stored as launch_rope_append
                      // would store it (q half, cache rows), without the fp32 round trip; see RopeEpilogue
-    EPI_ROPE_BS = 4  // chosen by the launcher for EPI_ROPE when RopeEpilogue::map names row scales: block-scaled cache rows, and
+    EPI_ROPE_BS = 4  // chosen by the tiled kernel's launcher for EPI_ROPE when RopeEpilogue::map names row scales: block-scaled cache rows, and
                      // q with its low half term
 };
 // What the EPI_ROPE epilogue needs: row m of the product is sequence b0 + m / T at position m % T (a prefill from
@@ -139,11 +139,10 @@ struct PackedGemmArgs {
 };
 bool gemm_packed_rope_supported(int M, int K, int64_t lda, int Hq, int hd, int rope_style);
 bool gemm_packed_single_launch(int N, int K);  // the matrix is served by one launch (no row slabs): candidates are possible
-// M of any size (row blocks of 128 re-stream the weights; meant for M <= 256).
+// M of any size: the weights stream once for few rows (decode steps); the row blocks of many rows (prefill) share them in L2.
 void launch_gemm_packed(const PackedGemmArgs &a, hipStream_t st);
 // Fused gate/up projection (EPI_SWIGLU) of few rows from the copies, K halves on separate wavefronts: the sums are
-// formed in the order of launch_gemm_skinny's and equal them bit for bit.  a.P[0] = gate, a.P[1] = up, a.rows[0] = F;
-// a.depth: weight chunks (128 wide) in flight per wavefront, 2 or 4 (0: 4).
+// formed in the order of launch_gemm_skinny's and equal them bit for bit.  a.P[0] = gate, a.P[1] = up, a.rows[0] = F.
 bool gemm_packed_swiglu_halves_supported(int F, int K);
 void launch_gemm_packed_swiglu_halves(const PackedGemmArgs &a, hipStream_t st);
 void gemm_packed_plan(int N, int K, int M, int *nb, int *rows_per_wg, int *splits);

@@ -312,8 +312,8 @@ int project(rl_gen *h, int cls, const f16_t *A, const f16_t *A_lo, int64_t lda, 
     if (acc_out) {
         if (a.A_lo && P0 && !W1 && !W2) {
             // two activation terms from the fragment-order copy: 128-row workgroups of the decode kernel, two per compute
-            // unit (they hide each other's barriers and epilogues), run 3-6 % ahead of the tile kernel (16384 rows, 7B shape:
-            // O 1.06 against 1.09 ms, down 2.47 against 2.59); with one term the tile kernel is ahead
+            // unit (they hide each other's barriers and epilogues), run ahead of the tile kernel (16384 rows, 7B shape: O 0.88
+            // against 0.95 ms, down 2.27 against 2.59); with one term the tile kernel is ahead
             PackedGemmArgs q;
             q.A = A; q.A_lo = A_lo; q.lda = lda; q.M = M; q.K = K;
             q.P[0] = P0; q.P[1] = nullptr; q.P[2] = nullptr;
@@ -1542,7 +1542,7 @@ int rl_op_gemm_packed_swiglu_halves(const uint16_t *A, int64_t lda, const uint16
     a.P[0] = Pg; a.P[1] = Pu; a.P[2] = nullptr;
     a.rows[0] = F; a.rows[1] = F; a.rows[2] = 0;
     a.out = out; a.ldc = ldc; a.split_stride = 0; a.splits = 1; a.epilogue = EPI_SWIGLU; a.out_lo = out_lo;
-    a.nb = 2; a.rows_per_wg = 128; a.depth = depth;
+    a.nb = 2; a.rows_per_wg = 128; a.depth = 2;
     launch_gemm_packed_swiglu_halves(a, reinterpret_cast<hipStream_t>(st));
     RL_OP_RETURN();
 }

@@ -584,10 +584,11 @@ def test_paged_cache_equals_contiguous_cache(graph, page):
     paged.close()
 
 
-def test_paged_ragged_prefill_through_the_fused_projection_and_grouped_query_attention():
+@pytest.mark.parametrize("packed", [True, False])
+def test_paged_ragged_prefill_through_the_fused_projection_and_grouped_query_attention(packed):
     """A model wide enough for the kernels the small paged tests do not reach: head_dim 128 with 4 query heads per kv head
     (matrix-core decode attention through page lists) and a prefill of 2880 rows (QKV projection that rotates and appends
-    in its epilogue, honouring page lists and per-sequence lengths).  Paged equals contiguous bit for bit; two sequences
+    in its epilogue, honouring page lists and per-sequence lengths: the packed kernel over copies, the tile kernel without).  Paged equals contiguous bit for bit; two sequences
     are checked against the oracle run alone."""
     from paper_2406_14088_amd import Generator
     shape = ModelShape(1, 4096, 32, 8, 128, 1024, 1000)
@@ -612,10 +613,10 @@ def test_paged_ragged_prefill_through_the_fused_projection_and_grouped_query_att
         torch.cuda.synchronize()
         return out
 
-    flat = Generator(shape, Wg, B, T + steps)
+    flat = Generator(shape, Wg, B, T + steps, packed=packed)
     want = run(flat)
     flat.close()
-    paged = Generator(shape, Wg, B, T + steps, page_size=page, n_pages=n_pages)
+    paged = Generator(shape, Wg, B, T + steps, packed=packed, page_size=page, n_pages=n_pages)
     paged.set_block_table(_shuffled_pages(capacity, page, n_pages, 52), capacity)
     got = run(paged)
     paged.close()
