@@ -209,7 +209,8 @@ int rl_gen_read_state(rl_gen_t *h, int32_t *lens, int32_t *done, void *hip_strea
  * (bytes of its tokens so far); a paged cache moves nothing: the page lists move, the caller's own copy of them has to follow
  * `kept`, and the pages of the dropped sequences are the caller's again.  With n == current batch nothing changes; with
  * n == 0 the generator is left without sequences, as after rl_gen_reset.  Per-sequence results of later steps are
- * the same as without compaction (rows of a batch do not interact).
+ * the same as without compaction (rows of a batch do not interact): bit for bit from a batch of at most 128 sequences with
+ * fragment-order copies; otherwise some sums may be formed in another order on fewer rows.
  * Errors: RL_GEN_E_NULL, RL_GEN_E_STATE (no sequences), RL_GEN_E_CAPACITY (more than 8192 sequences), RL_GEN_E_HIP. */
 int rl_gen_compact(rl_gen_t *h, int32_t *tokens, int32_t *kept, int32_t *n_kept, void *hip_stream);
 

@@ -138,8 +138,8 @@ __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_pa
     //      XCD and its L2.  Few row blocks: the row blocks of one (tile, split) -- which stream the same weights -- get ids
     //      8 apart, so the weights come from HBM once and from that L2 for the other row blocks.  Many row blocks
     //      (p.group_z, prefill): an XCD walks its share of the tiles in groups of PK_GROUP_Z row blocks, so that its 64 resident
-    //      workgroups form a block of 4 x 16 tiles and share both operands in L2.  (One column tile at a time would have every
-    //      XCD read all activation rows once per tile: 12 GB from memory in 2.6 ms at 16384 rows.  16384 rows, two terms,
+    //      workgroups form a block of 4 x 16 tiles and share both operands in L2.  (One column tile at a time has every XCD
+    //      read all activation rows once per tile: 12.3 GB fetched by a gate/up call of 16384 rows, 7.3 GB in groups.  16384 rows, two terms,
     //      N = 12288, K = 4096: 2622 -> 2423-2510 us; O 921 -> 882, down 2369 -> 2272, one-term gate/up 2547 -> 2450-2525.  Groups
     //      of 8: level but down 2338; of 16 and 32: as before or slower.)
     const int id = blockIdx.x;
