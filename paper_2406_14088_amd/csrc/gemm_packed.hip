@@ -378,8 +378,8 @@ __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_pa
                 // elements 4 c .. + 3 and their partners 64 + 4 c .. + 3, so the table row, the head row and its low term move
                 // as whole 128-byte lines and the row maximum is four shuffles.  The arithmetic is rope_append_kernel's,
                 // operation for operation.  While one workgroup is here the other one of the compute unit multiplies; the
-                // tile kernel's epilogue, one workgroup per compute unit, adds 0.5-0.65 ms to a call (16384 rows of the 7B
-                // shape, two terms, block-scaled rows: 3350 us there, 2770 here; the plain fp32 store 2464).
+                // tile kernel's epilogue, one workgroup per compute unit, adds 0.4-0.5 ms to a call (16384 rows of the 7B
+                // shape, two terms, block-scaled rows: 3290 us there over a plain store of 2880; 2520 here over 2490).
                 if (ncols > 0) {
                     const RopeEpilogue &rp = p.rope;
                     const int head = n_first >> 7, c = t & 15;

@@ -333,8 +333,8 @@ int project(rl_gen *h, int cls, const f16_t *A, const f16_t *A_lo, int64_t lda, 
 }
 
 // QKV projection of a prefill from the fragment-order copies: 128-row workgroups of the packed kernel, whose epilogue rotates q
-// and k and stores q and the cache rows.  16384 rows of the 7B shape: two terms and block-scaled rows 2770 us (tile kernel
-// 3350), one term and half rows 1436 (2232).
+// and k and stores q and the cache rows.  16384 rows of the 7B shape: two terms and block-scaled rows 2520 us (tile kernel
+// from copies 3290, from row-major weights 3430), one term and half rows 1440 (2134 from copies).
 // Tiles of 128 rows x 256 columns are fewer than half the compute units for short prompts and narrow models: tiles of 64 x 128 then
 // (the same sums in the same order).  Two terms, us per layer with 128 x 256 tiles / 64 x 128 tiles / the tile kernel and the separate
 // rotary kernel: 32/8 heads of hidden 4096, 260 rows 100 / 46 / 88, 640 rows (120 tiles) 111 / 73 / 104; 64/8 heads of hidden 8192,
