@@ -2,48 +2,107 @@
 // the same prefill pass has just written into the cache (tiled, online softmax, f16 MFMA).
 //
 // Layout of the computation for gfx950 (wavefront = 64 lanes, v_mfma_f32_32x32x16_f16):
-//   * workgroup = 4 wavefronts = 128 consecutive query positions of one (sequence, query head);
+//   * workgroup = NW wavefronts = 32 NW consecutive query positions of one (sequence, query head);
 //     wavefront w owns 32 of them and keeps its Q fragments in registers for the whole kernel;
-//   * key tiles of 32 positions are staged once per workgroup in LDS (K and V, padded rows);
 //   * scores are computed TRANSPOSED, S^T = K Q^T, so that in the accumulator layout a lane holds one
 //     query column and 16 key rows: the softmax statistics of a query are lane-local (one shuffle
 //     joins the two half-wavefronts), and the probabilities already sit in the register layout of the
 //     B operand of the second product O^T += V^T P^T -- no shuffle or LDS round trip for P;
-//   * V^T fragments are gathered from the LDS tile with 16-bit reads (the transpose happens there).
-// Softmax and accumulation are fp32; probabilities are rounded to half for the matrix cores.
+//   * a tile of 8 NW cache rows is staged once per workgroup: the rows of tile i + 1 are in flight (registers) while
+//     tile i is multiplied, are then converted and stored to the other of two LDS buffers, and one barrier ends the trip;
+//   * V is stored transposed, the keys of a row in the order in which the accumulator holds the probabilities, so a V^T
+//     fragment is one 16-byte LDS read.
+// Softmax and accumulation are fp32; probabilities are rounded to half for the matrix cores (two terms over block-scaled rows).
+//
+// What bounds it: long prompts the matrix cores together with the vector work of the softmax (691-853 TFLOP/s executed at 2048 and
+// 4096 positions); short ones the chain fetch -> convert -> barrier of their few tiles.  A version with 128 queries per workgroup,
+// 16-bit gathers from untransposed V (128 LDS reads per 32 keys and wavefront instead of 16), a single buffer and every element
+// scaled in fp32 on its way to LDS kept the matrix cores 10 % busy.  us a launch, that version -> this one, block-scaled rows, 32
+// heads: 8 x 2048 positions 3516 -> 1203, 32 x 512 997 -> 483, 32 x 384 467 -> 316, 37 x 205 288 -> 182, 128 x 128 380 -> 265,
+// 1 x 128 18 -> 19; half rows, 32/8 heads, 16 x 1024 682 -> 426.
+// Error of the two-term output against 64 bits (normal rows, scores of deviation 1.5, before -> now): 128 keys 3.05e-7 -> 2.27e-7,
+// 333 keys 3.67e-7 -> 2.76e-7, 1000 keys 4.61e-7 -> 3.49e-7; scores all equal 1.82e-7 -> 1.85e-7.
 #include "kernels.h"
 
-#define PA_THREADS 256
-#define PA_KT 32          // keys per tile
-#define PA_STRIDE(HD) ((HD) + 8)
+#define PA_PSHIFT 10       // probabilities over block-scaled rows are split at this power of two above their value, ...
+#define PA_PSCALE 1024.f   // ... which keeps the low term of a small one out of the subnormal halves
 
-// I16: the cache rows are 16-bit block-scaled fixed point (KvMap::kscale / vscale).  A row element q * scale has more
+// Staging of block-scaled rows.  Two int16 elements n -> the two-term half split of n / 64 (both exact: hi = n / 64 rounded to
+// half, lo = the rest, a multiple of 1/64).  The bits 15..6 and 5..0 become halves by placing them in the mantissa of 1024, so
+// everything is packed 16-bit arithmetic and no element is ever widened; the row scales are applied to the scores (K) and to the
+// probabilities (V) in fp32 instead.
+__device__ __forceinline__ void pa_split_i16x2(uint32_t n, uint32_t &hi, uint32_t &lo) {
+    typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+    const uint32_t top = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2_t, n) >> 6) ^ 0x66006600u;  // 1024 + (n >> 6) + 512
+    const uint32_t bot = (n & 0x003f003fu) | 0x64006400u;                                                 // 1024 + (n & 63)
+    const f16x2_t a = __builtin_bit_cast(f16x2_t, top) - (_Float16)1536.f;
+    const f16x2_t b = __builtin_bit_cast(f16x2_t, bot) * (_Float16)0.015625f - (_Float16)16.f;
+    const f16x2_t s = a + b;  // |a| >= |b| or a = 0: the rounding error of the sum is b - (s - a), exactly
+    hi = __builtin_bit_cast(uint32_t, s);
+    lo = __builtin_bit_cast(uint32_t, b - (s - a));
+}
+
+// 4 rows x 4 columns of 16-bit values (two packed words per row) -> the 4 columns, 4 rows each
+__device__ __forceinline__ void pa_transpose4(const u32x2_t (&r)[4], u32x2_t (&c)[4]) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        c[2 * p].x = __builtin_amdgcn_perm(r[1][p], r[0][p], 0x05040100u);
+        c[2 * p].y = __builtin_amdgcn_perm(r[3][p], r[2][p], 0x05040100u);
+        c[2 * p + 1].x = __builtin_amdgcn_perm(r[1][p], r[0][p], 0x07060302u);
+        c[2 * p + 1].y = __builtin_amdgcn_perm(r[3][p], r[2][p], 0x07060302u);
+    }
+}
+
+// LDS of one buffer: K [terms][KT][HD + 8] and V^T [terms][HD][KT + 8] halves, then (block-scaled rows) the score factors and
+// the normalised value scales [KT] and the value reference of the tile.  Both row strides are 4 banks modulo 16, which keeps
+// the 16-byte fragment reads free of conflicts; the 16-byte pieces of a V^T row are permuted by the row's 16-row group so that the
+// transposing 8-byte stores of a wavefront spread over all banks.
+template <int HD, bool I16, int NW>
+struct PaTile {
+    static constexpr int KT = 8 * NW, NT = I16 ? 2 : 1;
+    static constexpr int KSTR = HD + 8, VSTR = KT + 8;
+    static constexpr int K_HALVES = NT * KT * KSTR, V_HALVES = NT * HD * VSTR;
+    static constexpr int BYTES = (K_HALVES + V_HALVES) * 2 + (I16 ? (2 * KT + 4) * 4 : 0);
+    __device__ static __forceinline__ int v_at(int term, int dim, int piece) {
+        return (term * HD + dim) * VSTR + ((piece ^ (dim >> 4)) & (KT / 8 - 1)) * 8;
+    }
+};
+
+// I16: the cache rows are 16-bit block-scaled fixed point (KvMap::kscale / vscale).  A row element has more
 // significant bits than a half holds, so it enters the matrix cores as a two-term half sum hi + lo, and so do the
 // probabilities and -- when q_lo is given -- the queries: each of the two products of a tile becomes three matrix
 // instructions (hi x hi, lo x hi, hi x lo; lo x lo is below fp32 resolution) and no operand carries a single half rounding.
+// A probability is multiplied with its row's value scale before it is split; so that the product stays in the normal range of a
+// half, scales are taken relative to a power of two, the one at or below the largest scale up to the tile at hand (the reference, part
+// of the online rescale).
 // q_lo (optional, I16 only): second half term of q, laid out like q.
 // out_lo (optional): half(o - half(o)), the second term of the output for a two-term output projection.
-template <int HD, bool I16>
-__global__ __launch_bounds__(PA_THREADS) void prefill_attention_kernel(const f16_t *__restrict__ q,
-                                                                      const f16_t *__restrict__ q_lo,
-                                                                      const f16_t *__restrict__ kc,
-                                                                      const f16_t *__restrict__ vc,
-                                                                      f16_t *__restrict__ out, f16_t *__restrict__ out_lo,
-                                                                      int b0, int T, int Hq,
-                                                                      int Hkv, int S, KvMap map,
-                                                                      const int32_t *__restrict__ d_valid) {
+// xcd_heads > 0: heads of all sequences, a multiple of 8; the workgroups of one head and of its neighbours run on one XCD, whose
+// L2 then reads their cache rows once.
+template <int HD, bool I16, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16_t *__restrict__ q, const f16_t *__restrict__ q_lo,
+                                                                       const f16_t *__restrict__ kc, const f16_t *__restrict__ vc,
+                                                                       f16_t *__restrict__ out, f16_t *__restrict__ out_lo, int b0,
+                                                                       int T, int Hq, int Hkv, int S, KvMap map,
+                                                                       const int32_t *__restrict__ d_valid, int xcd_heads) {
+    using L = PaTile<HD, I16, NW>;
+    constexpr int KT = L::KT, NT = L::NT, THREADS = 64 * NW, ROWS = 32 * NW;
     constexpr int KS = HD / 16;   // k16 steps of the QK product
     constexpr int ET = HD / 32;   // 32-row tiles of O^T
-    constexpr int STR = PA_STRIDE(HD);
-    constexpr int NT = I16 ? 2 : 1;  // half terms per cache element
-    __shared__ __attribute__((aligned(16))) f16_t ks[NT * PA_KT * STR];
-    __shared__ __attribute__((aligned(16))) f16_t vs[NT * PA_KT * STR];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6, half = lane >> 5, l32 = lane & 31;
-    const int qt = blockIdx.x;          // query tile (128 positions)
-    const int u = blockIdx.y;           // query head
-    const int bl = blockIdx.z;          // sequence within the chunk
+    constexpr int KP = HD / 64;   // 16-byte pieces of K per thread and tile: KT * HD / 8 = KP * THREADS
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), half = lane >> 5, l32 = lane & 31;
+    int qt = blockIdx.x, u = blockIdx.y, bl = blockIdx.z;  // query tile, query head, sequence within the chunk
+    if (xcd_heads) {
+        const int id = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, xcd = id & 7, nth = id >> 3;
+        const int head = xcd * (xcd_heads >> 3) + nth / (int)gridDim.x;
+        qt = nth % (int)gridDim.x;
+        u = head % Hq;
+        bl = head / Hq;
+    }
+    qt = gridDim.x - 1 - qt;  // the longest rows first
     const int kvh = u / (Hq / Hkv);
-    const int q0 = qt * 128 + w * 32;   // first query position of this wavefront
+    const int q0 = qt * ROWS + w * 32;  // first query position of this wavefront
     const int qpos = q0 + l32;          // this lane's query column
     const size_t ldq = (size_t)Hq * HD;
 
@@ -72,120 +131,213 @@ __global__ __launch_bounds__(PA_THREADS) void prefill_attention_kernel(const f16
     for (int e = 0; e < ET; ++e)
 #pragma unroll
         for (int i = 0; i < 16; ++i) oacc[e][i] = 0.f;
-    float mrun = -INFINITY, lrun = 0.f;  // running max (shared by both halves) and this half's partial sum
-    const float scale = rsqrtf((float)HD);
+    float mrun = -INFINITY, lrun = 0.f;  // running max (shared by both halves) and this half's partial sum, base 2
+    float vref = 0.f;                    // value reference the accumulators are relative to
+    const float c2 = rsqrtf((float)HD) * 1.44269504088896340736f;  // scores times this are exponents of 2
 
-    int last_q = qt * 128 + 127;
-    if (last_q > T - 1) last_q = T - 1;
-    const int n_tiles = last_q / PA_KT + 1;  // key tiles any wavefront of the workgroup needs
-    for (int kt = 0; kt < n_tiles; ++kt) {
-        __syncthreads();  // previous tile fully consumed
-        // stage K and V rows kt*32 .. +31: 32 rows x HD*2 bytes each = HD/8 16-byte pieces per row
-        for (int idx = t; idx < PA_KT * (HD / 8); idx += PA_THREADS) {
-            int row = idx / (HD / 8), piece = idx % (HD / 8);
-            int key = kt * PA_KT + row;
-            u32x4_t kv = {0u, 0u, 0u, 0u}, vv = {0u, 0u, 0u, 0u};
-            float ksc = 0.f, vsc = 0.f;
-            if (key < n_keys) {  // rows past the prompt may hold arbitrary bits: keep them out (0 * NaN)
+    // ---- staging: K as rows (16-byte pieces), V as groups of 4 rows x 4 columns, the scales by the first KT threads (wavefront 0)
+    constexpr int VG = (KT / 4) * (HD / 4);  // 4 x 4 groups of a tile (one per thread at most)
+    u32x4_t kreg[KP];
+    u32x2_t vreg[4];
+    float kscr = 0.f, vscr = 0.f, vmax_run = 0.f;
+    auto fetch = [&](int kt) {
+#pragma unroll
+        for (int i = 0; i < KP; ++i) {
+            const int idx = t + i * THREADS, key = kt * KT + idx / (HD / 8);
+            kreg[i] = u32x4_t{0u, 0u, 0u, 0u};
+            if (key < n_keys)  // rows past the prompt may hold arbitrary bits: keep them out (0 * NaN)
+                kreg[i] = *reinterpret_cast<const u32x4_t *>(kc + kv_row_index(map, b0 + bl, kvh, Hkv, S, key) * HD + (idx % (HD / 8)) * 8);
+        }
+        const int key4 = kt * KT + t / (HD / 4) * 4;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) vreg[r] = u32x2_t{0u, 0u};
+        if (t < VG && key4 < n_keys) {  // 4 aligned rows share a page (a page holds a power of two >= 16)
+            const f16_t *vp = vc + kv_row_index(map, b0 + bl, kvh, Hkv, S, key4) * HD + (t % (HD / 4)) * 4;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (key4 + r < n_keys) vreg[r] = *reinterpret_cast<const u32x2_t *>(vp + r * HD);
+        }
+        if (I16 && w == 0) {
+            const int key = kt * KT + lane;
+            kscr = 0.f;
+            vscr = 0.f;
+            if (lane < KT && key < n_keys) {
                 const size_t rowi = kv_row_index(map, b0 + bl, kvh, Hkv, S, key);
-                const size_t at = rowi * HD + piece * 8;
-                kv = *reinterpret_cast<const u32x4_t *>(kc + at);
-                vv = *reinterpret_cast<const u32x4_t *>(vc + at);
-                if (I16) { ksc = map.kscale[rowi]; vsc = map.vscale[rowi]; }
+                kscr = map.kscale[rowi];
+                vscr = map.vscale[rowi];
             }
+        }
+    };
+    auto stash = [&](int buf) {
+        f16_t *ks = reinterpret_cast<f16_t *>(smem + buf * L::BYTES), *vs = ks + L::K_HALVES;
+#pragma unroll
+        for (int i = 0; i < KP; ++i) {
+            const int idx = t + i * THREADS;
+            f16_t *at = ks + idx / (HD / 8) * L::KSTR + (idx % (HD / 8)) * 8;
             if (I16) {
                 u32x4_t hi, lo;
-                auto split = [](u32x4_t w, float sc, u32x4_t &h, u32x4_t &l) {
-                    const uint32_t in[4] = {w.x, w.y, w.z, w.w};
-                    uint32_t ho[4], lo_[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float x0 = i16lo_to_f32(in[i]) * sc, x1 = i16hi_to_f32(in[i]) * sc;
-                        ho[i] = pack_f16x2(x0, x1);
-                        lo_[i] = pack_f16x2_lo(x0, x1, ho[i]);
-                    }
-                    h = u32x4_t{ho[0], ho[1], ho[2], ho[3]};
-                    l = u32x4_t{lo_[0], lo_[1], lo_[2], lo_[3]};
-                };
-                split(kv, ksc, hi, lo);
-                *reinterpret_cast<u32x4_t *>(ks + row * STR + piece * 8) = hi;
-                *reinterpret_cast<u32x4_t *>(ks + (PA_KT + row) * STR + piece * 8) = lo;
-                split(vv, vsc, hi, lo);
-                *reinterpret_cast<u32x4_t *>(vs + row * STR + piece * 8) = hi;
-                *reinterpret_cast<u32x4_t *>(vs + (PA_KT + row) * STR + piece * 8) = lo;
+                for (int j = 0; j < 4; ++j) {
+                    uint32_t h, l;
+                    pa_split_i16x2(kreg[i][j], h, l);
+                    hi[j] = h;
+                    lo[j] = l;
+                }
+                *reinterpret_cast<u32x4_t *>(at) = hi;
+                *reinterpret_cast<u32x4_t *>(at + KT * L::KSTR) = lo;
             } else {
-                *reinterpret_cast<u32x4_t *>(ks + row * STR + piece * 8) = kv;
-                *reinterpret_cast<u32x4_t *>(vs + row * STR + piece * 8) = vv;
+                *reinterpret_cast<u32x4_t *>(at) = kreg[i];
             }
         }
-        __syncthreads();
-        if (kt * PA_KT > q0 + 31) continue;  // tile entirely above this wavefront's diagonal (uniform per wavefront)
+        if (t < VG) {
+            // rows 8a + 4h + 0..3 of a 32-row block are slots 4 (a & 1) + 0..3 of the fragment (step a / 2, half-wavefront h)
+            const int g = t / (HD / 4), dim = (t % (HD / 4)) * 4;
+            const int piece = (g >> 3) * 4 + ((g >> 2) & 1) * 2 + (g & 1), slot = ((g >> 1) & 1) * 4;
+            u32x2_t col[4], low[4];
+            if (I16) {
+                u32x2_t hi[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        uint32_t h, l;
+                        pa_split_i16x2(vreg[r][p], h, l);
+                        hi[r][p] = h;
+                        low[r][p] = l;
+                    }
+                pa_transpose4(hi, col);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x2_t *>(vs + L::v_at(0, dim + i, piece) + slot) = col[i];
+                pa_transpose4(low, col);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x2_t *>(vs + L::v_at(1, dim + i, piece) + slot) = col[i];
+            } else {
+                pa_transpose4(vreg, col);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x2_t *>(vs + L::v_at(0, dim + i, piece) + slot) = col[i];
+            }
+        }
+        if (I16 && w == 0) {
+            float *sc = reinterpret_cast<float *>(vs + L::V_HALVES);
+            vmax_run = fmaxf(vmax_run, wave_max(vscr < INFINITY ? vscr : 0.f));
+            // the power of two at or below the largest scale: taking it out is exact
+            const float ref = vmax_run > 0.f ? fmaxf(__uint_as_float(__float_as_uint(vmax_run) & 0x7f800000u), 1.17549435e-38f) : 0.f;
+            if (lane < KT) {
+                sc[lane] = kscr * (64.f * c2);
+                // below 2 PA_PSCALE by construction; the clamp keeps a row of infinities from reaching queries that do not see it
+                sc[KT + lane] = ref > 0.f ? fminf(ldexpf(vscr, PA_PSHIFT - ilogbf(ref)), 2.f * PA_PSCALE) : 0.f;
+            }
+            if (lane == 0) sc[2 * KT] = ref;
+        }
+    };
 
-        // S^T tile: rows = keys, columns = queries
-        f32x16_t sacc;
+    int last_q = qt * ROWS + ROWS - 1;
+    if (last_q > T - 1) last_q = T - 1;
+    const int n_tiles = last_q / KT + 1;  // key tiles any wavefront of the workgroup needs
+    fetch(0);
+    stash(0);
+    __syncthreads();
+    for (int kt = 0; kt < n_tiles; ++kt) {
+        const bool more = kt + 1 < n_tiles;
+        if (more) fetch(kt + 1);
+        const f16_t *ks = reinterpret_cast<const f16_t *>(smem + (kt & 1) * L::BYTES), *vs = ks + L::K_HALVES;
+        const float *sc = reinterpret_cast<const float *>(vs + L::V_HALVES);
+#pragma unroll 1
+        for (int sub = 0; sub < KT / 32; ++sub) {
+            const int key0 = kt * KT + sub * 32;
+            if (key0 > q0 + 31 || q0 >= T) break;  // above this wavefront's diagonal, or no query (uniform per wavefront)
+            // The small products of a two-term operand are summed on their own: 8 instead of 24 roundings at the magnitude of the
+            // score (with one accumulator the output error over 333 keys is a quarter larger), and two shorter chains.
+            f32x16_t sacc, slow;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
+            for (int i = 0; i < 16; ++i) sacc[i] = slow[i] = 0.f;
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-#pragma unroll
-            for (int tm = 0; tm < NT; ++tm) {
-                f16x8_t kf = *reinterpret_cast<const f16x8_t *>(ks + (tm * PA_KT + l32) * STR + half * 8 + s * 16);
-                sacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[s], sacc, 0, 0, 0);
-                if (I16 && tm == 0 && two_q) sacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, ql[s], sacc, 0, 0, 0);
-            }
-        }
-        // register i holds key row (i/4)*8 + half*4 + (i%4) of the tile, query column l32
-        float tmax = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            int key = kt * PA_KT + (i >> 2) * 8 + half * 4 + (i & 3);
-            float sv = key <= qpos ? sacc[i] * scale : -INFINITY;  // causal mask
-            sacc[i] = sv;
-            tmax = fmaxf(tmax, sv);
-        }
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-        float mnew = fmaxf(mrun, tmax);  // finite: key 0 is visible to every query
-        float alpha = mrun == -INFINITY ? 0.f : __expf(mrun - mnew);
-        mrun = mnew;
-        lrun *= alpha;
-#pragma unroll
-        for (int e = 0; e < ET; ++e)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[e][i] *= alpha;
-        f16x8_t pf[2], pl[I16 ? 2 : 1];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            float p = __expf(sacc[i] - mnew);
-            lrun += p;
-            const _Float16 ph = (_Float16)p;
-            pf[i >> 3][i & 7] = ph;
-            if (I16) pl[i >> 3][i & 7] = (_Float16)(p - (float)ph);
-        }
-        // O^T += V^T P^T.  Slot j of k-step s in lane-half h stands for key (2s + j/4)*8 + h*4 + j%4 -- the
-        // key that accumulator register s*8 + j already holds, so P needs no data movement.
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-#pragma unroll
-            for (int e = 0; e < ET; ++e) {
+            for (int s = 0; s < KS; ++s) {
 #pragma unroll
                 for (int tm = 0; tm < NT; ++tm) {
-                    f16x8_t vf;
+                    f16x8_t kf = *reinterpret_cast<const f16x8_t *>(ks + (tm * KT + sub * 32 + l32) * L::KSTR + half * 8 + s * 16);
+                    if (tm == 0) sacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[s], sacc, 0, 0, 0);
+                    else slow = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[s], slow, 0, 0, 0);
+                    if (I16 && tm == 0 && two_q) slow = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, ql[s], slow, 0, 0, 0);
+                }
+            }
+            if (I16) sacc += slow;
+            // register i holds key row (i/4)*8 + half*4 + (i%4) of the block, query column l32
+            float rel = 1.f, vnew = 0.f;
+            if (I16) vnew = sc[2 * KT];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        int krow = (2 * s + (j >> 2)) * 8 + half * 4 + (j & 3);
-                        vf[j] = __builtin_bit_cast(_Float16, vs[(tm * PA_KT + krow) * STR + e * 32 + l32]);
+            for (int i4 = 0; i4 < 4; ++i4) {
+                f32x4_t f = {c2, c2, c2, c2};
+                if (I16) f = *reinterpret_cast<const f32x4_t *>(sc + sub * 32 + i4 * 8 + half * 4);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) sacc[i4 * 4 + j] *= f[j];
+            }
+            if (key0 + 31 > q0) {  // the diagonal block: causal mask
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (key0 + (i >> 2) * 8 + half * 4 + (i & 3) > qpos) sacc[i] = -INFINITY;
+            }
+            float tmax = sacc[0];
+#pragma unroll
+            for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, sacc[i]);
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+            const float mnew = fmaxf(mrun, tmax);  // finite: key 0 is visible to every query
+            if (I16 && vnew != vref) rel = vref / vnew;  // powers of two; the reference only grows, so it is positive here
+            if (__any(mnew != mrun) || rel != 1.f) {
+                const float alpha = __builtin_amdgcn_exp2f(mrun - mnew);
+                lrun *= alpha;
+#pragma unroll
+                for (int e = 0; e < ET; ++e)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) oacc[e][i] *= alpha * rel;
+                mrun = mnew;
+                vref = vnew;
+            }
+            f16x8_t pf[2], pl[I16 ? 2 : 1];
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+                f32x4_t f = {1.f, 1.f, 1.f, 1.f};
+                if (I16) f = *reinterpret_cast<const f32x4_t *>(sc + KT + sub * 32 + i4 * 8 + half * 4);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int i = i4 * 4 + j;
+                    float p = __builtin_amdgcn_exp2f(sacc[i] - mnew);
+                    lrun += p;
+                    if (I16) {
+                        p *= f[j];
+                        // The product is a value of its own: contracted into the conversion, one use of ph would come from the
+                        // unrounded product and the other from the rounded one, and where these fall on different halves the two
+                        // terms miss p by a half's spacing (2.0e-6 instead of 3.7e-7 over 333 keys).
+                        asm("" : "+v"(p));
                     }
-                    oacc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf[s], oacc[e], 0, 0, 0);
-                    if (I16 && tm == 0) oacc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pl[s], oacc[e], 0, 0, 0);
+                    const _Float16 ph = (_Float16)p;
+                    pf[i >> 3][i & 7] = ph;
+                    if (I16) pl[i >> 3][i & 7] = (_Float16)(p - (float)ph);
+                }
+            }
+            // O^T += V^T P^T.  Slot j of k-step s in lane-half h stands for key (2s + j/4)*8 + h*4 + j%4 -- the
+            // key that accumulator register s*8 + j already holds, so P needs no data movement.
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+#pragma unroll
+                for (int e = 0; e < ET; ++e) {
+#pragma unroll
+                    for (int tm = 0; tm < NT; ++tm) {
+                        f16x8_t vf = *reinterpret_cast<const f16x8_t *>(vs + L::v_at(tm, e * 32 + l32, sub * 4 + s * 2 + half));
+                        oacc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf[s], oacc[e], 0, 0, 0);
+                        if (I16 && tm == 0) oacc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pl[s], oacc[e], 0, 0, 0);
+                    }
                 }
             }
         }
+        if (more) stash((kt + 1) & 1);  // the buffer of tile kt - 1: read before the last barrier
+        __syncthreads();
     }
 
     // normalise and store: lane = query column; register i of tile e is head_dim row e*32 + (i/4)*8 + half*4 + i%4
     float ltot = lrun + __shfl_xor(lrun, 32, 64);
     if (qpos < T) {
-        float inv = 1.0f / ltot;
+        float inv = (I16 ? vref * (64.f / PA_PSCALE) : 1.0f) / ltot;
         f16_t *op = out + ((size_t)bl * T + qpos) * ldq + (size_t)u * HD;
 #pragma unroll
         for (int e = 0; e < ET; ++e)
@@ -205,14 +357,32 @@ __global__ __launch_bounds__(PA_THREADS) void prefill_attention_kernel(const f16
     }
 }
 
+template <int HD, bool I16, int NW>
+static void launch_pa(const f16_t *q, const f16_t *q_lo, const f16_t *kc, const f16_t *vc, f16_t *out, f16_t *out_lo, int nb, int b0,
+                      int T, int Hq, int Hkv, int S, const KvMap &map, const int32_t *d_valid, hipStream_t st) {
+    constexpr int lds = 2 * PaTile<HD, I16, NW>::BYTES;
+    static_assert(lds <= 160 * 1024, "two buffers fit a compute unit");
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_attention_kernel<HD, I16, NW>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    (void)attr;
+    dim3 grid(ceil_div(T, 32 * NW), Hq, nb);
+    const int64_t heads = (int64_t)Hq * nb;
+    const int xcd_heads = heads % 8 == 0 && heads * grid.x < (1ll << 31) ? (int)heads : 0;
+    prefill_attention_kernel<HD, I16, NW><<<grid, 64 * NW, lds, st>>>(q, q_lo, kc, vc, out, out_lo, b0, T, Hq, Hkv, S, map, d_valid, xcd_heads);
+}
+
 void launch_prefill_attention(const f16_t *q, const f16_t *kc, const f16_t *vc, f16_t *out, int nb, int b0, int T,
                               int Hq, int Hkv, int hd, int S, hipStream_t st, KvMap map, const int32_t *d_valid, f16_t *out_lo,
                               const f16_t *q_lo) {
     if (nb <= 0 || T <= 0) return;
-    dim3 grid(ceil_div(T, 128), Hq, nb);
     const bool i16 = map.kscale != nullptr;
-    if (hd == 128 && i16) prefill_attention_kernel<128, true><<<grid, PA_THREADS, 0, st>>>(q, q_lo, kc, vc, out, out_lo, b0, T, Hq, Hkv, S, map, d_valid);
-    else if (hd == 128) prefill_attention_kernel<128, false><<<grid, PA_THREADS, 0, st>>>(q, nullptr, kc, vc, out, out_lo, b0, T, Hq, Hkv, S, map, d_valid);
-    else if (i16) prefill_attention_kernel<64, true><<<grid, PA_THREADS, 0, st>>>(q, q_lo, kc, vc, out, out_lo, b0, T, Hq, Hkv, S, map, d_valid);
-    else prefill_attention_kernel<64, false><<<grid, PA_THREADS, 0, st>>>(q, nullptr, kc, vc, out, out_lo, b0, T, Hq, Hkv, S, map, d_valid);
+    const bool wide = T > 128;  // up to 128 positions the second half of a wide workgroup would hold no query
+    auto run = [&](auto kernel) { kernel(q, i16 ? q_lo : nullptr, kc, vc, out, out_lo, nb, b0, T, Hq, Hkv, S, map, d_valid, st); };
+    if (hd == 128) {
+        if (i16) wide ? run(launch_pa<128, true, 8>) : run(launch_pa<128, true, 4>);
+        else wide ? run(launch_pa<128, false, 8>) : run(launch_pa<128, false, 4>);
+    } else {
+        if (i16) wide ? run(launch_pa<64, true, 8>) : run(launch_pa<64, true, 4>);
+        else wide ? run(launch_pa<64, false, 8>) : run(launch_pa<64, false, 4>);
+    }
 }

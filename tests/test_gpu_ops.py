@@ -466,7 +466,7 @@ def test_decode_attention_fused_with_rope_and_append(ops, style, hd, Hq, Hkv, le
 
 
 @pytest.mark.parametrize("hd,Hq,Hkv", [(128, 4, 4), (128, 8, 2), (64, 4, 1)])
-@pytest.mark.parametrize("T", [1, 16, 100, 300])
+@pytest.mark.parametrize("T", [1, 16, 100, 128, 129, 300])
 def test_prefill_attention(ops, hd, Hq, Hkv, T):
     step(f"prefill attention hd={hd} Hq={Hq} Hkv={Hkv} T={T}")
     nb, b0, S, nseq = 2, 1, 320, 3
@@ -973,7 +973,7 @@ def test_decode_attention_at_long_context_lengths(ops, kind, length):
 
 
 @pytest.mark.parametrize("hd,Hq,Hkv", [(128, 4, 4), (128, 8, 2), (64, 4, 1)])
-@pytest.mark.parametrize("T", [1, 16, 100, 300])
+@pytest.mark.parametrize("T", [1, 16, 100, 128, 129, 300])
 def test_prefill_attention_block_scaled_rows_and_two_term_output(ops, hd, Hq, Hkv, T):
     """Prefill attention over int16 * scale rows: every element enters the matrix cores as hi + lo, so only q and the
     probabilities carry a half rounding."""
@@ -1000,6 +1000,36 @@ def test_prefill_attention_block_scaled_rows_and_two_term_output(ops, hd, Hq, Hk
                 small = 3e-5 * (1 + np.abs(vn[b0 + b, u // g, : i + 1]).max())
                 assert (np.abs(on[b, i, u] - ref) <= 0.5 * F16_EPS * np.abs(ref) * 1.02 + small).all(), (b, u, i)
                 assert (np.abs(on[b, i, u] + ln[b, i, u] - ref) <= small + 2e-6 * np.abs(ref)).all(), (b, u, i, np.abs(on[b, i, u] + ln[b, i, u] - ref).max())
+
+
+@pytest.mark.parametrize("hd,T", [(128, 33), (128, 128), (128, 129), (64, 333), (128, 700)])
+def test_prefill_attention_two_term_error_against_64_bits(ops, hd, T):
+    """Row scales that differ by a factor of 50, queries, rows and output in two terms: nothing but fp32 rounding is left.  A score is
+    the sum of about 16 roundings of 2^-24, an output that of its keys' weights and 6 T / 32 products per lane, all of random sign:
+    below 2^-24 * sqrt(16 + 6 * T / 32) * 4 < 1e-6 up to 700 keys in the 2-norm.  A term that belongs to another rounding
+    of the same value (a half's spacing once in 2^13) is 2e-6."""
+    H, S = 4, T + 7
+    qf = randn_f32((T, H * hd), 195, std=1.5)
+    q = qf.to(torch.float16)
+    q_lo = (qf - q.float()).to(torch.float16)
+    ramp = torch.exp(torch.linspace(-2, 2, S, device=DEV))[torch.randperm(S, generator=torch.Generator().manual_seed(198)).to(DEV)]
+    kc, ks, kn = _random_block_scaled((1, H, S, hd), 196)
+    vc, vs, vn = _random_block_scaled((1, H, S, hd), 197)
+    vs = (vs * ramp).contiguous()
+    vn = np64(vc) * np64(vs)[..., None]
+    out = torch.zeros((T, H * hd), dtype=torch.float16, device=DEV)
+    out_lo = torch.zeros_like(out)
+    ops.prefill_attention(q, kc, vc, out, 1, 0, T, H, H, hd, S, kscale=ks, vscale=vs, out_lo=out_lo, q_lo=q_lo)
+    torch.cuda.synchronize()
+    qn = (np64(q) + np64(q_lo)).reshape(T, H, hd)
+    got = (np64(out) + np64(out_lo)).reshape(T, H, hd)
+    err = ref2 = 0.0
+    for u in range(H):
+        for i in range(0, T, 3):
+            ref = orc.attend(qn[i, u], kn[0, u, : i + 1], vn[0, u, : i + 1])
+            err += ((got[i, u] - ref) ** 2).sum()
+            ref2 += (ref ** 2).sum()
+    assert np.sqrt(err / ref2) < 1e-6, np.sqrt(err / ref2)
 
 
 @pytest.mark.parametrize("M,K,F,kind", [(4, 256, 688, "halves"), (128, 512, 1000, "halves"), (77, 1000, 200, "packed"),
