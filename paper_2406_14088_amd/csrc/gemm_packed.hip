@@ -470,7 +470,7 @@ __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_pa
             for (int e = 0; e < 16; ++e) {
                 int m = mt * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
                 float g = acc[0][mt][e], u = acc[NB - 1][mt][e];
-                const float y = g / (1.0f + expf(-g)) * u;
+                const float y = silu_mul(g, u);
                 const f16_t hi = f32_to_f16(y);
                 ht[m * PK_HT_STRIDE + w * 32 + (lane & 31)] = hi;
                 if (two_out) ht[(BM + m) * PK_HT_STRIDE + w * 32 + (lane & 31)] = f32_to_f16(y - f16_to_f32(hi));
@@ -716,34 +716,41 @@ __global__ __launch_bounds__(PK_THREADS, 1) void gemm_packed_swiglu_halves_kerne
     __builtin_amdgcn_s_waitcnt(0);  // copies issued for chunks past the end (zeros) must have landed before the memory is reused
     __syncthreads();
 
-    // ---- half 0 + half 1: kg = 1 hands its sums to kg = 0 (same operand order as the row-major kernel)
-    float *ex = reinterpret_cast<float *>(smem);  // [2 column halves][2 MT 16][64 lanes]
-    if (kg == 1) {
+    // ---- half 0 + half 1.  Of every 32-row tile, wavefront kg finishes accumulator registers 8 kg .. + 7 and gives the others away,
+    //      so that all four wavefronts share the SwiGLU.  (With the sums of both halves finished by the kg = 0 wavefronts, expf and an
+    //      IEEE division the epilogue took 9.5 of 54 us at 128 rows of FFN 11008 and 2.4 of 34 at one row.)  The order of the sum
+    //      is that of the row-major kernel.
+    f32x4_t *ex = reinterpret_cast<f32x4_t *>(smem);  // [4 wavefronts][2 MT 2][64 lanes] of four registers
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) ex[((cw * 2 + j) * MT * 16 + mt * 16 + e) * 64 + lane] = acc[j][mt][e];
-    }
-    __syncthreads();
-    f16_t *ht = reinterpret_cast<f16_t *>(smem + 2 * 2 * MT * 16 * 64 * 4);  // 2 x [BM][72] halves (both terms), after the exchange area
-    const bool two_out = p.out_lo != nullptr;
-    if (kg == 0) {
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                float g = acc[0][mt][e], u = acc[1][mt][e];
-                g += ex[((cw * 2 + 0) * MT * 16 + mt * 16 + e) * 64 + lane];
-                u += ex[((cw * 2 + 1) * MT * 16 + mt * 16 + e) * 64 + lane];
-                int m = mt * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-                const float y = g / (1.0f + expf(-g)) * u;
+            for (int q = 0; q < 2; ++q) {
+                f32x4_t v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = kg ? acc[j][mt][4 * q + e] : acc[j][mt][8 + 4 * q + e];
+                ex[(w * 4 * MT + (j * MT + mt) * 2 + q) * 64 + lane] = v;
+            }
+    __syncthreads();
+    f16_t *ht = reinterpret_cast<f16_t *>(smem + 4 * 4 * MT * 64 * 16);  // 2 x [BM][72] halves (both terms), after the exchange area
+    const bool two_out = p.out_lo != nullptr;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            f32x4_t g = ex[((w ^ 2) * 4 * MT + mt * 2 + q) * 64 + lane], u = ex[((w ^ 2) * 4 * MT + (MT + mt) * 2 + q) * 64 + lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                g[e] += kg ? acc[0][mt][8 + 4 * q + e] : acc[0][mt][4 * q + e];  // two summands: either order gives the same bits
+                u[e] += kg ? acc[1][mt][8 + 4 * q + e] : acc[1][mt][4 * q + e];
+                const int m = mt * 32 + (2 * kg + q) * 8 + (lane >> 5) * 4 + e;
+                const float y = silu_mul(g[e], u[e]);
                 const f16_t hi = f32_to_f16(y);
                 ht[m * 72 + cw * 32 + (lane & 31)] = hi;
                 if (two_out) ht[(BM + m) * 72 + cw * 32 + (lane & 31)] = f32_to_f16(y - f16_to_f32(hi));
             }
-    }
+        }
     __syncthreads();
     const int c8 = (t & 7) * 8, rr = t >> 3;  // 8 lanes x 16 B = one 128-byte output row; 32 rows per pass
     const int ncols = rows - tile * 64;
@@ -775,7 +782,7 @@ __global__ __launch_bounds__(PK_THREADS, 1) void gemm_packed_swiglu_halves_kerne
 template <int MT, bool SW>
 static void launch_halves(PackedParams &p, hipStream_t st) {
     size_t lds = (size_t)3 * 2 * 32 * MT * 64 * 2;  // three chunk buffers
-    const size_t epi = (size_t)2 * 2 * MT * 16 * 64 * 4 + (size_t)2 * 32 * MT * 72 * 2;  // exchange area + both output tiles
+    const size_t epi = (size_t)4 * 4 * MT * 64 * 16 + (size_t)2 * 32 * MT * 72 * 2;  // exchange area + both output tiles
     if (epi > lds) lds = epi;
     static bool attr_set = false;
     if (!attr_set) {

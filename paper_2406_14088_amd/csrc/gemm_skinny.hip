@@ -272,7 +272,7 @@ __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams
                 for (int j = 0; j < 16; ++j) {
                     int m = mt * 32 + (j >> 2) * 8 + (lane >> 5) * 4 + (j & 3);
                     float g = acc[mt][j], u = ex[(ng * MT * 16 + mt * 16 + j) * 64 + lane];
-                    ht[m * 72 + ng * 32 + (lane & 31)] = f32_to_f16(g / (1.0f + expf(-g)) * u);
+                    ht[m * 72 + ng * 32 + (lane & 31)] = f32_to_f16(silu_mul(g, u));
                 }
         }
         __syncthreads();

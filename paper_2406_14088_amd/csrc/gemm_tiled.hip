@@ -290,7 +290,7 @@ __device__ __forceinline__ void tiled_epilogue(const TiledParams &p, const TileC
 #pragma unroll
                         for (int e = 0; e < 16; ++e) {
                             float g = acc[i][j][e], u = ex[(j * 16 + e) * 64 + lane];
-                            float a = g / (1.0f + expf(-g)) * u;
+                            float a = silu_mul(g, u);
                             const f16_t hi = f32_to_f16(a);
                             ht[((e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)) * (2 * CT) + j * 32 + (lane & 31)] =
                                 tm == 0 ? hi : f32_to_f16(a - f16_to_f32(hi));

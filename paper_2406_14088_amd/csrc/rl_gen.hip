@@ -368,7 +368,7 @@ bool swiglu_project(rl_gen *h, const f16_t *A, const f16_t *A_lo, f16_t *out_lo,
     const bool copies = h->packed && l < h->packed_gu_layers;
     // Up to 128 rows and FFN widths up to 16384: the kernel that puts the K halves of each chunk on separate wavefronts (the
     // row-major kernel's sums in its order, from the copies).  Against the packed kernel at 1 / 64 / 128 rows: FFN 11008
-    // 34 / 40 / 51 us (46 / 54 / 57); FFN 14336 40 / 45 / 55 us (49 / 57 / 60); the row-major kernel takes 52 and 63 us at 128
+    // 32 / 39 / 47 us (46 / 54 / 57); FFN 14336 40 / 42 / 51 us (49 / 57 / 60); the row-major kernel takes 52 and 63 us at 128
     // rows.  Wider FFNs (K = 8192 shapes) and more rows stay with the packed kernel (34B shape at 64 rows: 137 against 160 us).
     if (copies && !A_lo && M <= 128 && h->s.ffn <= 256 * 64 && gemm_packed_swiglu_halves_supported(h->s.ffn, h->s.hidden)) {
         PackedGemmArgs q;

@@ -1032,6 +1032,30 @@ def test_prefill_attention_two_term_error_against_64_bits(ops, hd, T):
     assert np.sqrt(err / ref2) < 1e-6, np.sqrt(err / ref2)
 
 
+@pytest.mark.parametrize("M", [1, 33, 100])
+def test_swiglu_gate_range(ops, M):
+    """Gates from far below to far above where e^-g leaves fp32: out + out_lo is the fp64 value to 22 bits of a two-term sum (2^-22), a
+    few roundings of fp32 and, below the normal halves, the 2^-25 grid of the low term."""
+    F, K = 512, 64
+    gates = torch.cat([torch.linspace(-100, 100, F - 8), torch.tensor([-3e4, -300.0, -88.0, -87.0, 0.0, 88.0, 300.0, 3e4])])
+    Wg, Wu = torch.zeros((F, K)), torch.zeros((F, K))
+    Wg[:, 0], Wu[:, 1] = gates, torch.linspace(-2, 2, F)
+    Wg, Wu = Wg.to(torch.bfloat16).to(DEV), Wu.to(torch.bfloat16).to(DEV)
+    A = torch.zeros((M, K), dtype=torch.float16, device=DEV)
+    A[:, 0], A[:, 1] = 1.0, torch.linspace(0.5, 1.5, M, device=DEV).half()
+    P = []
+    for w in (Wg, Wu):
+        P.append(torch.empty((ops.packed_weight_bytes(F, K) // 2,), dtype=torch.int16, device=DEV))
+        ops.pack_weights(w, P[-1])
+    out = torch.zeros((M, F), dtype=torch.float16, device=DEV)
+    out_lo = torch.zeros_like(out)
+    ops.gemm_packed_swiglu_halves(A, P[0], P[1], F, K, out, F, M=M, out_lo=out_lo)
+    torch.cuda.synchronize()
+    g, u = np64(A) @ np64(Wg).T, np64(A) @ np64(Wu).T
+    ref = g / (1 + np.exp(-np.clip(g, -700, 700))) * u
+    assert (np.abs(np64(out) + np64(out_lo) - ref) <= 2.0 ** -21 * np.abs(ref) + 2.0 ** -24).all()
+
+
 @pytest.mark.parametrize("M,K,F,kind", [(4, 256, 688, "halves"), (128, 512, 1000, "halves"), (77, 1000, 200, "packed"),
                                         (300, 256, 688, "packed"), (600, 264, 520, "tiled")])
 def test_swiglu_two_term_output(ops, M, K, F, kind):
