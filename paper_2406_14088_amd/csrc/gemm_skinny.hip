@@ -29,10 +29,8 @@
 #define SK_BK 128            // K elements per chunk
 #define SK_LDS_STRIDE 136    // half elements per LDS row of the activation tile (128 + 8 pad -> 272 B)
 #define SK_THREADS 512
-#define SK_BM 128            // activation rows per workgroup (grid.z walks taller batches)
-#define SK_MT 4              // 32-row MFMA tiles per workgroup
 #define SK_OOB 0xFFFFFF00u   // byte offset beyond every descriptor (< 4 GiB - 256): such a load returns zeros, touches no memory
-#define SK_X_BYTES (2 * SK_BM * SK_LDS_STRIDE * 2)   // two activation buffers
+#define SK_X_BYTES(MT) (2 * 32 * (MT) * SK_LDS_STRIDE * 2)  // two activation buffers
 #define SK_W_BYTES (8 * 2 * 4096)                    // per wavefront: two strips of 32 rows x 128 B
 #define SK_CT_STRIDE 132                             // floats per row of the fp32 output tile in LDS
 
@@ -54,9 +52,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint3
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
 }
 
+// MT: 32-row tiles of activations per workgroup (1, 2 or 4; grid.z walks taller batches): the matrix instructions, the staging and the
+// epilogue of 128 rows cost a batch of 16 as much as one of 128.
+template <int MT>
 __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int MT = SK_MT, BM = SK_BM;
+    constexpr int BM = 32 * MT;
     f16_t *xs = reinterpret_cast<f16_t *>(smem);  // [2][BM][SK_LDS_STRIDE]
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);  // wavefront id as a scalar: descriptors stay in SGPRs
@@ -93,7 +94,7 @@ __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams
     // wavefront-private LDS strip, [2][32 rows][8 pieces of 16 B]; piece j of row r sits in slot j ^ ((r >> 1) & 7):
     // 64 banks = 256 bytes = two rows per clock, and a fragment read has 16 consecutive rows in the 16 lanes served
     // together, so the slot changes every second row
-    unsigned char *wl = smem + SK_X_BYTES + w * 8192;
+    unsigned char *wl = smem + SK_X_BYTES(MT) + w * 8192;
     int wst[4];  // store address of instruction i (row = lane/8 + 8i)
 #pragma unroll
     for (int i = 0; i < 4; ++i) wst[i] = (lane >> 3) * 128 + (((lane & 7) ^ (((8 * i + (lane >> 3)) >> 1) & 7)) << 4);
@@ -175,7 +176,7 @@ __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams
             }
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[s & 1][mt], wf[s & 1], acc[mt], 0, 0, 0);
-            store_x1(PAR ^ 1, PAR ^ 1, s);               // activation piece s of chunk c+1 (loaded one chunk ago)
+            if (s < MT) store_x1(PAR ^ 1, PAR ^ 1, s);   // activation piece s of chunk c+1 (loaded one chunk ago)
             stage_w1((PAR ^ 1) * 4 + s, PAR ^ 1, s);     // weight piece s of chunk c+1: ring -> strip
             load_w1(c + 3, (PAR ^ 1) * 4 + s, s);        // and refill its ring slot
             __builtin_amdgcn_sched_barrier(0);
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams
         const int c8 = (t & 7) * 8, rr = t >> 3;  // 8 lanes x 16 B = one 128-byte output row; 64 rows per pass
         const int ncols = rows - tile * 64;
 #pragma unroll
-        for (int i = 0; i < BM / 64; ++i) {
+        for (int i = 0; i < (BM + 63) / 64; ++i) {
             int m = rr + 64 * i;
             if (m < Mloc && c8 < ncols) {
                 f16_t *dst = out + (size_t)(m0 + m) * p.ldc + tile_col + c8;
@@ -304,6 +305,14 @@ int gemm_skinny_default_splits(int M, int N, int K) {
     if (s > chunks / 4) s = chunks / 4 > 0 ? chunks / 4 : 1;  // keep at least 4 chunks per split
     if (s > 16) s = 16;
     return s;
+}
+
+template <int MT>
+static void launch_skinny(const SkinnyParams &p, dim3 grid, hipStream_t st) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_skinny_kernel<MT>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    (void)attr;
+    gemm_skinny_kernel<MT><<<grid, SK_THREADS, SK_X_BYTES(MT) + SK_W_BYTES, st>>>(p);
 }
 
 void launch_gemm_skinny(const GemmArgs &a, hipStream_t st) {
@@ -334,12 +343,8 @@ void launch_gemm_skinny(const GemmArgs &a, hipStream_t st) {
     if (a.epilogue == EPI_SWIGLU) tiles = ceil_div(a.rows[0], 64);
     p.tile_begin[3] = tiles;
     if (tiles <= 0) return;
-    size_t lds = SK_X_BYTES + SK_W_BYTES;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_skinny_kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        attr_set = true;
-    }
-    gemm_skinny_kernel<<<dim3(tiles, p.splits, ceil_div(a.M, SK_BM)), SK_THREADS, lds, st>>>(p);
+    const dim3 grid(tiles, p.splits, ceil_div(a.M, a.M <= 32 ? 32 : (a.M <= 64 ? 64 : 128)));
+    if (a.M <= 32) launch_skinny<1>(p, grid, st);
+    else if (a.M <= 64) launch_skinny<2>(p, grid, st);
+    else launch_skinny<4>(p, grid, st);
 }
