@@ -9,7 +9,7 @@
 //     rows (= output columns) and multiplies the half kg (64 elements = one 128-byte line per row) of
 //     every 128-wide K chunk; the two K halves are added through LDS at the end (fixed order);
 //   * weights are fetched with fully coalesced loads (8 lanes x 16 B = one line of one row, 8 rows per
-//     instruction), kept in flight in an 8-register ring two chunks ahead, widened bf16 -> half in
+//     instruction), kept in flight in a register ring of two to four chunks, widened bf16 -> half in
 //     registers (exact for normal halves), parked in a wavefront-private, XOR-swizzled LDS strip and read
 //     back as MFMA fragments (lane = weight row, 8 consecutive k) without bank conflicts; the strip is
 //     private to the wavefront, so this needs no barrier;
@@ -54,10 +54,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint3
 
 // MT: 32-row tiles of activations per workgroup (1, 2 or 4; grid.z walks taller batches): the matrix instructions, the staging and the
 // epilogue of 128 rows cost a batch of 16 as much as one of 128.
-template <int MT>
+// SW: one row block, every weight byte is used once and is loaded non-temporally (streams faster than a cached load).
+template <int MT, bool SW>
 __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int BM = 32 * MT;
+    constexpr int BM = 32 * MT, R = MT <= 2 ? 4 : 2;  // R: chunks in flight
     f16_t *xs = reinterpret_cast<f16_t *>(smem);  // [2][BM][SK_LDS_STRIDE]
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);  // wavefront id as a scalar: descriptors stay in SGPRs
@@ -115,9 +116,8 @@ __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams
         int row = r0 + 32 * i;
         x_off[i] = (uint32_t)(m0 + row) * (uint32_t)p.lda_bytes + (uint32_t)c16 * 16u;
     }
-    u32x4_t xr[2][MT];  // activation pieces in flight: xr[i & 1] belongs to chunk c0 + i
-    const bool stream_w = gridDim.z == 1;
-    u32x4_t wq[8];      // raw bf16 weight pieces in flight: slots (i & 1) * 4 .. + 3 belong to chunk c0 + i
+    u32x4_t xr[R][MT];  // activation pieces in flight: xr[i % R] belongs to chunk c0 + i
+    u32x4_t wq[4 * R];  // raw bf16 weight pieces in flight: slots (i % R) * 4 .. + 3 belong to chunk c0 + i
     f32x16_t acc[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -140,24 +140,24 @@ __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams
     };
     auto load_w1 = [&](int c, int slot, int i) {  // piece i of chunk c -> ring slot
         uint32_t cb = (uint32_t)c * (SK_BK * 2);
-        // one row block: every weight byte is used once and is loaded non-temporally (streams faster than a cached load)
-        if (stream_w) wq[slot] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)(c < c1 ? w_off[i] + cb : SK_OOB), 0, 3);
-        else wq[slot] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)(c < c1 ? w_off[i] + cb : SK_OOB), 0, 0);
+        wq[slot] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)(c < c1 ? w_off[i] + cb : SK_OOB), 0, SW ? 3 : 0);
     };
     auto stage_w1 = [&](int slot, int buf, int i) {  // ring slot -> half -> LDS strip `buf`
         *reinterpret_cast<u32x4_t *>(wl + buf * 4096 + i * 1024 + wst[i]) = bf16x8_to_f16x8(wq[slot]);
     };
 
-    // One chunk (index i relative to c0, PAR = i & 1): MFMAs on the strip/tile staged one chunk ago.
+    // One chunk (index i relative to c0, SLOT = i % R): MFMAs on the strip/tile staged one chunk ago.
     // Interleaved with its four k-steps, piece by piece: the next chunk's activations move registers ->
-    // LDS tile, the next chunk's weights move ring -> half -> LDS strip, and the ring is refilled three
-    // chunks ahead, so that the matrix cores, the LDS and the memory pipeline work at the same time.
-    // The hardware counts outstanding loads in issue order: all (short-latency, L2) activation loads of a
-    // trip are issued before its weight loads, so waiting for them never waits for young weight loads.
-    auto body = [&](int c, auto par_tag) {
-        constexpr int PAR = decltype(par_tag)::value;
+    // LDS tile, the next chunk's weights move ring -> half -> LDS strip, and the ring is refilled R + 1 chunks
+    // ahead, so that the matrix cores, the LDS and the memory pipeline work at the same time.
+    // Loads return in issue order: waiting for the activations of a chunk waits for every weight load issued before them.  The
+    // activations are therefore requested as far ahead as the weights -- with two chunks in flight the weights of one and a half
+    // trips at most were (R = 2 -> 4: gate/up 4096 -> 11008 of 16 rows 43.8 -> 41.4 us, of 64 rows 48.8 -> 46.3; QKV, O and down level).
+    // 128 rows have no registers for it.
+    auto body = [&](int c, auto slot_tag) {
+        constexpr int SLOT = decltype(slot_tag)::value, NEXT = (SLOT + 1) % R, PAR = SLOT & 1;
         __syncthreads();  // activation tile of chunk c is in LDS buffer PAR; buffer PAR^1 is free
-        load_x(c + 2, PAR);
+        load_x(c + R, SLOT);
         const f16_t *src = xs + (size_t)PAR * BM * SK_LDS_STRIDE + (lane & 31) * SK_LDS_STRIDE + (lane >> 5) * 8 + kg * 64;
         const unsigned char *wsrc = wl + PAR * 4096;
         f16x8_t a[2][MT];
@@ -176,30 +176,36 @@ __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams
             }
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[s & 1][mt], wf[s & 1], acc[mt], 0, 0, 0);
-            if (s < MT) store_x1(PAR ^ 1, PAR ^ 1, s);   // activation piece s of chunk c+1 (loaded one chunk ago)
-            stage_w1((PAR ^ 1) * 4 + s, PAR ^ 1, s);     // weight piece s of chunk c+1: ring -> strip
-            load_w1(c + 3, (PAR ^ 1) * 4 + s, s);        // and refill its ring slot
+            if (s < MT) store_x1(NEXT, PAR ^ 1, s);   // activation piece s of chunk c+1
+            stage_w1(NEXT * 4 + s, PAR ^ 1, s);       // weight piece s of chunk c+1: ring -> strip
+            load_w1(c + 1 + R, NEXT * 4 + s, s);      // and refill its ring slot
             __builtin_amdgcn_sched_barrier(0);
         }
     };
 
     if (c0 < c1) {
-        load_x(c0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) load_w1(c0, i, i);
+        for (int r = 0; r < R; ++r) {
+            load_x(c0 + r, r);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) load_w1(c0 + r, r * 4 + i, i);
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < MT; ++i) store_x1(0, 0, i);
-        load_x(c0 + 1, 1);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) load_w1(c0 + 1, 4 + i, i);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) stage_w1(i, 0, i);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) load_w1(c0 + 2, i, i);
+        for (int i = 0; i < 4; ++i) {
+            stage_w1(i, 0, i);
+            load_w1(c0 + R, i, i);
+        }
         __builtin_amdgcn_sched_barrier(0);
-        for (int c = c0; c < c1; c += 2) {
+        for (int c = c0; c < c1; c += R) {  // trips past the end multiply zero tiles
             body(c, std::integral_constant<int, 0>{});
             body(c + 1, std::integral_constant<int, 1>{});
+            if constexpr (R == 4) {
+                body(c + 2, std::integral_constant<int, 2>{});
+                body(c + 3, std::integral_constant<int, 3>{});
+            }
         }
     }
 
@@ -307,12 +313,12 @@ int gemm_skinny_default_splits(int M, int N, int K) {
     return s;
 }
 
-template <int MT>
+template <int MT, bool SW>
 static void launch_skinny(const SkinnyParams &p, dim3 grid, hipStream_t st) {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_skinny_kernel<MT>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_skinny_kernel<MT, SW>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     (void)attr;
-    gemm_skinny_kernel<MT><<<grid, SK_THREADS, SK_X_BYTES(MT) + SK_W_BYTES, st>>>(p);
+    gemm_skinny_kernel<MT, SW><<<grid, SK_THREADS, SK_X_BYTES(MT) + SK_W_BYTES, st>>>(p);
 }
 
 void launch_gemm_skinny(const GemmArgs &a, hipStream_t st) {
@@ -344,7 +350,8 @@ void launch_gemm_skinny(const GemmArgs &a, hipStream_t st) {
     p.tile_begin[3] = tiles;
     if (tiles <= 0) return;
     const dim3 grid(tiles, p.splits, ceil_div(a.M, a.M <= 32 ? 32 : (a.M <= 64 ? 64 : 128)));
-    if (a.M <= 32) launch_skinny<1>(p, grid, st);
-    else if (a.M <= 64) launch_skinny<2>(p, grid, st);
-    else launch_skinny<4>(p, grid, st);
+    if (a.M <= 32) launch_skinny<1, true>(p, grid, st);
+    else if (a.M <= 64) launch_skinny<2, true>(p, grid, st);
+    else if (a.M <= 128) launch_skinny<4, true>(p, grid, st);
+    else launch_skinny<4, false>(p, grid, st);
 }

@@ -1032,6 +1032,20 @@ def test_prefill_attention_two_term_error_against_64_bits(ops, hd, T):
     assert np.sqrt(err / ref2) < 1e-6, np.sqrt(err / ref2)
 
 
+@pytest.mark.parametrize("M", [1, 32, 33, 64, 65, 129])
+@pytest.mark.parametrize("K,splits", [(128, 1), (520, 1), (1160, 2), (1664, 3), (640, 1)])
+def test_gemm_skinny_row_tiles(ops, M, K, splits):
+    """Edges of the row tiles (32, 64, 128), chunk counts around the depth of the ring (1, 5, 10, 13 in splits, 5)."""
+    N = 200
+    A, W = randn_f16((M, K), 300), randn_bf16((N, K), 301, std=0.05)
+    out = torch.full((splits, M, N), 7.0, dtype=torch.float32, device=DEV)
+    ops.gemm(A, [W], out, N, M=M, split_stride=M * N, splits=splits, epilogue=0, kernel=1)
+    torch.cuda.synchronize()
+    a, w = np64(A), np64(W)
+    bound = 2.0 ** -24 * (K + splits) * (np.abs(a) @ np.abs(w).T)  # every fp32 addition of the sum rounds once
+    assert (np.abs(np64(out).sum(0) - a @ w.T) <= bound).all()
+
+
 @pytest.mark.parametrize("M", [1, 33, 100])
 def test_swiglu_gate_range(ops, M):
     """Gates from far below to far above where e^-g leaves fp32: out + out_lo is the fp64 value to 22 bits of a two-term sum (2^-22), a
