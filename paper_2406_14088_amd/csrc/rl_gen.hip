@@ -1499,7 +1499,7 @@ int rl_op_gemm_packed(const uint16_t *A, const uint16_t *A_lo, int64_t lda, cons
     a.out = out; a.ldc = ldc; a.split_stride = split_stride; a.splits = splits; a.epilogue = epilogue; a.out_lo = out_lo;
     int pnb, prows, psplits;
     gemm_packed_plan(rows0 + rows1 + rows2, K, M, &pnb, &prows, &psplits);
-    a.nb = nb == 0 ? pnb : nb;
+    a.nb = nb ? nb : (splits < psplits ? 1 : pnb);  // the wide workgroups of the plan come with its K split
     a.rows_per_wg = rows_per_wg;
     a.depth = depth;
     launch_gemm_packed(a, reinterpret_cast<hipStream_t>(st));
