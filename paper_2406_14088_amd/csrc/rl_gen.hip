@@ -1133,7 +1133,19 @@ int rl_gen_logprobs(rl_gen_t *h, const int32_t *tokens, int32_t B, int32_t T, fl
             {
                 Scope sc(h, RL_GEN_K_GEMM_LM_HEAD, st);
                 if (lo) a.A_lo = a.A + (size_t)M * s.hidden;
-                if (mm <= kSkinnyMaxM && !lo) launch_gemm_skinny(a, st);
+                if (h->packed) {
+                    // From the copy, in the workgroups of the other prefill projections (few rows: of the decode step).  A call of one
+                    // layer, tile kernel from row-major weights -> here, us: hidden 4096, vocabulary 32000, 12288 rows 10935 -> 10081,
+                    // 200 rows 441 -> 376, 40 rows 230 -> 215; vocabulary 128256, 4096 rows 12696 -> 9579; two terms, hidden 5120, 7992
+                    // rows 14281 -> 12767.
+                    PackedGemmArgs q;
+                    q.A = a.A; q.A_lo = a.A_lo; q.lda = a.lda; q.M = mm; q.K = a.K;
+                    q.P[0] = h->p_lm_head; q.P[1] = nullptr; q.P[2] = nullptr;
+                    q.rows[0] = s.vocab; q.rows[1] = 0; q.rows[2] = 0;
+                    q.out = a.out; q.ldc = s.vocab; q.split_stride = 0; q.splits = 1; q.epilogue = EPI_F32;
+                    q.nb = mm > kSkinnyMaxM ? 2 : 1; q.rows_per_wg = 128; q.depth = 2;
+                    launch_gemm_packed(q, st);
+                } else if (mm <= kSkinnyMaxM && !lo) launch_gemm_skinny(a, st);
                 else launch_gemm_tiled(a, st);
             }
             Scope sc(h, RL_GEN_K_MISC, st);
