@@ -839,16 +839,18 @@ void gemm_packed_plan(int N, int K, int M, int *nb, int *rows_per_wg, int *split
     if (s > 16) s = 16;
     if (s < 1) s = 1;
     *splits = s;
-    // Two row blocks that leave no K split: workgroups twice as wide over half of K.  A compute unit's loads return in order, activations
-    // from L2 behind weights from HBM, so what counts is the bytes it loads in all: twice the columns halve the activations.  Two
-    // terms, 256 rows, us: 15360 x 5120 94.6 -> 82.7, 12288 x 4096 70.2 -> 56.2; 160 rows 93.1 -> 75.8, 60.7 -> 55.3.  Where a K
-    // split is there already the additional partials cost what the activations save (13824 -> 5120 78.8 in 3 splits, 72.5 in 6 of the
-    // wide ones before their sum; 6144 x 4096 34.9 either way).
-    if (M > 128 && s == 1) {
-        const int wide = ceil_div(N, 256) * ceil_div(M, 128);
-        if (256 / wide >= 2 && chunks >= 16) {
+    // Workgroups twice as wide over half of K.  A compute unit's loads return in order, activations from L2 behind weights from HBM, so
+    // what counts is the bytes it loads in all, and twice the columns halve the activations; the price is twice the partials.
+    // Worth it where two row blocks leave no K split (two terms, 256 rows, us: 15360 x 5120 94.6 -> 82.7, 12288 x 4096 70.2 -> 56.2;
+    // 160 rows 93.1 -> 75.8, 60.7 -> 55.3) and where a split still is 64 chunks or more (28672 -> 8192, 48 / 64 / 128 rows 88.6 -> 80.1,
+    // 94.4 -> 84.5, 136 -> 126; 22016 -> 8192, 64 rows 75 -> 69); not for shorter ones (8192 -> 8192 of 64 rows, 32 chunks, 30.8 against
+    // 36.9; 14336 -> 4096 29.9 / 35.5).  Up to 32 rows either is level (28672 -> 8192 73 / 73, 78 / 77) and takes the same split: the
+    // sums of a batch of up to 128 rows keep their order when it shrinks.
+    if ((M > 128 && s == 1) || chunks / s >= 64) {
+        const int wide = ceil_div(N, 256) * ceil_div(M, *rows_per_wg);
+        if (2 * s <= 16 && wide * 2 * s <= 256 && chunks >= 16 * s) {
             *nb = 2;
-            *splits = 2;
+            *splits = 2 * s;
         }
     }
 }

@@ -244,6 +244,7 @@ PACKED_CASES = [
     (33, 688, (1000, 72), 3, 2, 1, 32), (128, 4096, (512, 128, 128), 4, 1, 2, 128), (200, 1024, (688,), 2, 2, 2, 64),
     (256, 512, (300,), 1, 1, 1, 32), (64, 264, (1024,), 1, 2, 1, 0), (128, 2048, (2048,), 16, 1, 1, 64), (77, 72, (40,), 1, 0, 1, 0),
     (130, 520, (1100, 200), 2, 1, 2, 32), (100, 1000, (2000,), 3, 2, 1, 64),
+    (16, 1160, (600,), 2, 2, 2, 32), (48, 1160, (600,), 3, 2, 2, 64), (100, 1160, (600, 40), 2, 2, 2, 128),
 ]
 
 
