@@ -334,10 +334,36 @@ __global__ __launch_bounds__(LP_THREADS) void logprob_gather_kernel(const float 
     }
     const float *row = logits + (size_t)blockIdx.x * ld;
     float m = -INFINITY, s = 0.f;
-    for (int i = t; i < V; i += LP_THREADS) {
-        float x = row[i];
-        if (x > m) { s = s * expf(m - x) + 1.f; m = x; }  // exp(-inf) = 0 on the first element
-        else s += expf(x - m);
+    // 16 elements a trip with one rescale, as 16-byte loads where the rows allow it.  (One element a trip, with a branch and expf, streamed
+    // the logits at 2.5 TB/s: 8192 rows of 32000 382 us, 197 now, 2048 of 128256 344, 186 now, at no larger error against 64 bits.)
+    auto add = [&](auto &x) {
+        constexpr int N = sizeof(x) / sizeof(float);
+        float mn = m;
+#pragma unroll
+        for (int k = 0; k < N; ++k) mn = fmaxf(mn, x[k]);
+        const float at = mn == -INFINITY ? 0.f : mn;  // nothing but zeros so far
+        s *= __builtin_amdgcn_exp2f((m - at) * 1.44269504f);
+#pragma unroll
+        for (int k = 0; k < N; ++k) s += __builtin_amdgcn_exp2f((x[k] - at) * 1.44269504f);
+        m = mn;
+    };
+    int i0 = 0;
+    if ((reinterpret_cast<uintptr_t>(row) & 15) == 0) {
+        i0 = V / (16 * LP_THREADS) * (16 * LP_THREADS);
+        for (int i = 4 * t; i < i0; i += 16 * LP_THREADS) {
+            float x[16];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const f32x4_t v = *reinterpret_cast<const f32x4_t *>(row + i + 4 * k * LP_THREADS);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[4 * k + e] = v[e];
+            }
+            add(x);
+        }
+    }
+    for (int i = i0 + t; i < V; i += LP_THREADS) {
+        float x[1] = {row[i]};
+        add(x);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) lse_merge(m, s, __shfl_xor(m, o, 64), __shfl_xor(s, o, 64));
