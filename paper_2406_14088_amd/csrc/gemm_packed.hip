@@ -524,7 +524,7 @@ static void launch_p2(PackedParams &p, hipStream_t st) {
     p.zblocks = ceil_div(p.M, BM);
     p.group_z = p.splits == 1 && grouped_tile_order(p.tiles, p.zblocks) ? 1 : 0;
     int ids = p.group_z ? ceil_div(p.tiles * p.zblocks, 8) * 8 : ceil_div(p.tiles * p.splits, 8) * 8 * p.zblocks;
-    if constexpr (((NB == 2 && MT == 4) || (NB == 1 && MT == 2)) && RC == 2 && !SW) {
+    if constexpr (((NB == 2 && MT == 4) || MT == 2) && RC == 2 && !SW) {
         if (p.epilogue == EPI_ROPE) {
             static bool rope_attr_set = false;
             if (!rope_attr_set) {
@@ -853,6 +853,19 @@ void gemm_packed_plan(int N, int K, int M, int *nb, int *rows_per_wg, int *split
             *splits = 2 * s;
         }
     }
+}
+
+// Tile of a projection of more rows than a decode step's, whole K per workgroup.  The smallest of 64 x 128, 64 x 256 and 128 x 256 (rows x
+// columns) that one workgroup per compute unit covers: a launch of fewer workgroups takes as long as one of them, so they should be
+// small, and of more than that the large tile moves the least bytes.  Two terms, us, 128 x 256 / 64 x 256 / 64 x 128: 4096 -> 4096, 260 rows 90 / 54
+// / 39, 512 rows 91 / 59 / 43, 700 rows (352 of the smallest) 90 / 61 / 66, 1000 rows 93 / 68 / 73, 1400 rows (352 of the middle) 102 / 99 / 97, 2048
+// rows 126 / 122 / 136; 11008 -> 4096, 512 rows 207 / 135 / 105, 1000 rows 214 / 160 / 177; 28672 -> 8192, 512 rows 542 / 407 / 489, 700 rows
+// (352 of the middle) 658 / 728 / 703.  The sums are the same in every tile.
+void gemm_packed_tile_plan(int M, const int rows[3], int *nb, int *rows_per_wg) {
+    auto tiles = [&](int width) { return (int64_t)ceil_div(rows[0], width) + ceil_div(rows[1], width) + ceil_div(rows[2], width); };
+    const int64_t z64 = ceil_div(M, 64);
+    *nb = tiles(128) * z64 <= 256 ? 1 : 2;
+    *rows_per_wg = tiles(128 * *nb) * z64 <= 256 ? 64 : 128;
 }
 
 // whether launch_gemm_packed serves a matrix in one launch (what the fused greedy choice needs)

@@ -135,7 +135,7 @@ struct PackedGemmArgs {
     float *cand_val = nullptr;
     int32_t *cand_idx = nullptr;
     bool no_store = false;
-    const RopeEpilogue *rope = nullptr;  // EPI_ROPE (gemm_packed_rope_supported): nb 2 and 128 rows per workgroup, or 1 and 64; depth 2
+    const RopeEpilogue *rope = nullptr;  // EPI_ROPE (gemm_packed_rope_supported): nb 2 and 128 rows per workgroup, or 64 rows; depth 2
 };
 bool gemm_packed_rope_supported(int M, int K, int64_t lda, int Hq, int hd, int rope_style);
 bool gemm_packed_single_launch(int N, int K);  // the matrix is served by one launch (no row slabs): candidates are possible
@@ -146,6 +146,7 @@ void launch_gemm_packed(const PackedGemmArgs &a, hipStream_t st);
 bool gemm_packed_swiglu_halves_supported(int F, int K);
 void launch_gemm_packed_swiglu_halves(const PackedGemmArgs &a, hipStream_t st);
 void gemm_packed_plan(int N, int K, int M, int *nb, int *rows_per_wg, int *splits);
+void gemm_packed_tile_plan(int M, const int rows[3], int *nb, int *rows_per_wg);  // prefill: no K split
 
 // ---- attention_decode.hip ------------------------------------------------------------------------
 // One new query per (sequence, query head) against cache rows 0 .. d_len[b * len_stride] (inclusive).

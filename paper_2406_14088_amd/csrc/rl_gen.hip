@@ -319,7 +319,8 @@ int project(rl_gen *h, int cls, const f16_t *A, const f16_t *A_lo, int64_t lda, 
             q.P[0] = P0; q.P[1] = nullptr; q.P[2] = nullptr;
             q.rows[0] = r0; q.rows[1] = 0; q.rows[2] = 0;
             q.out = acc_out; q.ldc = ld_acc; q.split_stride = 0; q.splits = 1; q.epilogue = EPI_F32_ACC;
-            q.nb = 2; q.rows_per_wg = 128; q.depth = 2;
+            gemm_packed_tile_plan(M, q.rows, &q.nb, &q.rows_per_wg);
+            q.depth = 2;
             launch_gemm_packed(q, st);
             return 0;
         }
@@ -335,12 +336,7 @@ int project(rl_gen *h, int cls, const f16_t *A, const f16_t *A_lo, int64_t lda, 
 // QKV projection of a prefill from the fragment-order copies: 128-row workgroups of the packed kernel, whose epilogue rotates q
 // and k and stores q and the cache rows.  16384 rows of the 7B shape: two terms and block-scaled rows 2520 us (tile kernel
 // from copies 3290, from row-major weights 3430), one term and half rows 1440 (2134 from copies).
-// Tiles of 128 rows x 256 columns are fewer than half the compute units for short prompts and narrow models: tiles of 64 x 128 then
-// (the same sums in the same order).  Two terms, us per layer with 128 x 256 tiles / 64 x 128 tiles / the tile kernel and the separate
-// rotary kernel: 32/8 heads of hidden 4096, 260 rows 100 / 46 / 88, 640 rows (120 tiles) 111 / 73 / 104; 64/8 heads of hidden 8192,
-// 260 rows (120) 201 / 124 / 177, 400 rows (160) 218 / 173 / 253; 8/8 heads of hidden 1024, 260 rows 40 / 18 / 31, 1024 rows (96)
-// 42 / 25 / 39, 2048 rows (192) 45 / 36 / 61; 32/32 heads of hidden 4096, 900 rows (384) 201 / 196 / 256, 2048 rows (768) 339 / 384 /
-// 518.  From 128 tiles on either is ahead of the tile kernel; which of the two is faster changes with the filling of the last round.
+// Short prompts and narrow models run in smaller tiles (gemm_packed_tile_plan).
 void rope_projection_from_copies(const f16_t *A, const f16_t *A_lo, int64_t lda, int M, int K, const f16_t *Pq, const f16_t *Pk,
                                  const f16_t *Pv, const RopeEpilogue &rp, hipStream_t st) {
     PackedGemmArgs q;
@@ -348,8 +344,8 @@ void rope_projection_from_copies(const f16_t *A, const f16_t *A_lo, int64_t lda,
     q.P[0] = Pq; q.P[1] = Pk; q.P[2] = Pv;
     q.rows[0] = rp.Hq * 128; q.rows[1] = rp.Hkv * 128; q.rows[2] = rp.Hkv * 128;
     q.out = nullptr; q.ldc = 0; q.split_stride = 0; q.splits = 1; q.epilogue = EPI_ROPE; q.rope = &rp;
-    const bool fills = (long)ceil_div(M, 128) * (ceil_div(rp.Hq, 2) + 2 * ceil_div(rp.Hkv, 2)) >= 128;
-    q.nb = fills ? 2 : 1; q.rows_per_wg = fills ? 128 : 64; q.depth = 2;
+    gemm_packed_tile_plan(M, q.rows, &q.nb, &q.rows_per_wg);
+    q.depth = 2;
     launch_gemm_packed(q, st);
 }
 

@@ -1047,6 +1047,28 @@ def test_gemm_skinny_row_tiles(ops, M, K, splits):
     assert (np.abs(np64(out).sum(0) - a @ w.T) <= bound).all()
 
 
+@pytest.mark.parametrize("M,N,K", [(257, 600, 264), (320, 256, 72), (449, 1100, 520)])
+@pytest.mark.parametrize("terms", [1, 2])
+def test_gemm_packed_tiles_of_a_prefill_store_the_same_bits(ops, M, N, K, terms):
+    """64 x 128, 64 x 256 and 128 x 256 tiles of an accumulating projection: the sums of an element do not depend on its tile."""
+    A, W = randn_f16((terms * M, K), 310), randn_bf16((N, K), 311, std=0.05)
+    P = torch.empty((ops.packed_weight_bytes(N, K) // 2,), dtype=torch.int16, device=DEV)
+    ops.pack_weights(W, P)
+    x = randn_f32((M, N), 312)
+    got = []
+    for nb, rows in ((1, 64), (2, 64), (2, 128)):
+        out = x.clone()
+        ops.gemm_packed(A[:M], [P], [N], K, out, N, A_lo=A[M:] if terms == 2 else None, M=M, split_stride=0, splits=1, epilogue=2, nb=nb,
+                        rows_per_wg=rows, depth=2)
+        got.append(out)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+    a = np64(A[:M]) + (np64(A[M:]) if terms == 2 else 0)
+    w = np64(W)
+    bound = 2.0 ** -24 * (terms * K + 1) * (np.abs(a) @ np.abs(w).T + np.abs(np64(x)))
+    assert (np.abs(np64(got[0]) - np64(x) - a @ w.T) <= 2 * bound).all()
+
+
 @pytest.mark.parametrize("M", [1, 33, 100])
 def test_swiglu_gate_range(ops, M):
     """Gates from far below to far above where e^-g leaves fp32: out + out_lo is the fp64 value to 22 bits of a two-term sum (2^-22), a
