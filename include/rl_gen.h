@@ -119,7 +119,7 @@ int rl_gen_create(const rl_gen_shape *shape, const rl_gen_weights *weights, void
  * (DEVICE, 256-byte aligned, at least rl_gen_packed_bytes long, caller-owned, borrowed while the handle
  * lives) in the order the matrix cores read them (IEEE half; layout in rl_gen_ops.h), enqueued on
  * hip_stream.  Afterwards steps of at most 256 rows (decode, short prefills) read the copies of these
- * matrices instead of the row-major weights; prefills of 1024 rows or more read them as the B operand of the large
+ * matrices instead of the row-major weights; larger prefills run from them too, in the same kernel or as the B operand of the large
  * tile kernel (copied global -> LDS directly; same bits as without).  Call it again after the weights changed (a training step
  * between two generation phases); packed_arena == NULL detaches the copies.  Results are the same to fp32
  * summation order with and without the copies.  Use the same stream as for the following steps, or
