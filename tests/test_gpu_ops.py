@@ -1093,6 +1093,34 @@ def test_swiglu_gate_range(ops, M):
     assert (np.abs(np64(out) + np64(out_lo) - ref) <= 2.0 ** -21 * np.abs(ref) + 2.0 ** -24).all()
 
 
+@pytest.mark.parametrize("M,kind", [(1, "halves"), (100, "halves"), (3, "packed"), (300, "packed"), (40, "skinny"), (300, "tiled")])
+def test_swiglu_infinite_gates(ops, M, kind):
+    """g / (1 + e^-g) * u at g = inf is inf (stored as the largest half, with u's sign), at g = -inf -inf / inf, a NaN (stored as minus
+    the largest half)."""
+    F, K = 136, 128
+    Wg, Wu = torch.zeros((F, K)), torch.zeros((F, K))
+    Wg[:, 0], Wu[:, 1] = torch.linspace(-4, 4, F), torch.where(torch.arange(F) % 3 == 0, -0.5, 2.0)
+    Wg[5::8, 0], Wg[6::8, 0] = float("inf"), float("-inf")
+    Wg, Wu = Wg.to(torch.bfloat16).to(DEV), Wu.to(torch.bfloat16).to(DEV)
+    A = torch.zeros((M, K), dtype=torch.float16, device=DEV)
+    A[:, 0], A[:, 1] = 1.0, torch.linspace(0.5, 1.5, M, device=DEV).half()
+    P = []
+    for w in (Wg, Wu):
+        P.append(torch.empty((ops.packed_weight_bytes(F, K) // 2,), dtype=torch.int16, device=DEV))
+        ops.pack_weights(w, P[-1])
+    out = torch.zeros((M, F), dtype=torch.float16, device=DEV)
+    if kind == "halves": ops.gemm_packed_swiglu_halves(A, P[0], P[1], F, K, out, F, M=M)
+    elif kind == "packed": ops.gemm_packed(A, P, [F, F], K, out, F, M=M, epilogue=1)
+    else: ops.gemm(A, [Wg, Wu], out, F, M=M, epilogue=1, kernel=1 if kind == "skinny" else 2)
+    torch.cuda.synchronize()
+    got, u = np64(out), np64(A) @ np64(Wu).T
+    assert (got[:, 5::8] == 65504 * np.sign(u[:, 5::8])).all() and (got[:, 6::8] == -65504).all()
+    fin = np.delete(np.arange(F), np.r_[5:F:8, 6:F:8])
+    g = np64(A) @ np64(Wg[fin.tolist()]).T
+    ref = g / (1 + np.exp(-g)) * u[:, fin]
+    assert (np.abs(got[:, fin] - ref) <= 2.0 ** -11 * 1.01 * np.abs(ref) + 2.0 ** -24).all()
+
+
 @pytest.mark.parametrize("M,K,F,kind", [(4, 256, 688, "halves"), (128, 512, 1000, "halves"), (77, 1000, 200, "packed"),
                                         (300, 256, 688, "packed"), (600, 264, 520, "tiled")])
 def test_swiglu_two_term_output(ops, M, K, F, kind):
