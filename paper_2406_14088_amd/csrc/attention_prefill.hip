@@ -22,10 +22,12 @@
 // 1 x 128 18 -> 19; half rows, 32/8 heads, 16 x 1024 682 -> 426.
 // Error of the two-term output against 64 bits (normal rows, scores of deviation 1.5, before -> now): 128 keys 3.05e-7 -> 2.27e-7,
 // 333 keys 3.67e-7 -> 2.76e-7, 1000 keys 4.61e-7 -> 3.49e-7; scores all equal 1.82e-7 -> 1.85e-7.
+#include <type_traits>
+
 #include "kernels.h"
 
-#define PA_PSHIFT 10       // probabilities over block-scaled rows are split at this power of two above their value, ...
-#define PA_PSCALE 1024.f   // ... which keeps the low term of a small one out of the subnormal halves
+#define PA_PSHIFT 14        // probabilities over block-scaled rows are split at this power of two above their value (products
+#define PA_PSCALE 16384.f   // with a scale stay below 2^15), which keeps the low term of a small one out of the subnormal halves
 
 // Staging of block-scaled rows.  Two int16 elements n -> the two-term half split of n / 64 (both exact: hi = n / 64 rounded to
 // half, lo = the rest, a multiple of 1/64).  The bits 15..6 and 5..0 become halves by placing them in the mantissa of 1024, so
@@ -53,8 +55,21 @@ __device__ __forceinline__ void pa_transpose4(const u32x2_t (&r)[4], u32x2_t (&c
     }
 }
 
+// largest of 32 lanes, in lanes 31 and 63 (values >= 0): register-to-register moves, a tenth of the latency of shuffles through LDS
+__device__ __forceinline__ float pa_max32(float v) {
+    auto from = [](float x, auto ctrl) {  // the lanes that the move does not reach get 0
+        return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    v = fmaxf(v, from(v, std::integral_constant<int, 0x111>{}));  // lane - 1, - 2, - 4, - 8 of the same 16
+    v = fmaxf(v, from(v, std::integral_constant<int, 0x112>{}));
+    v = fmaxf(v, from(v, std::integral_constant<int, 0x114>{}));
+    v = fmaxf(v, from(v, std::integral_constant<int, 0x118>{}));
+    return fmaxf(v, from(v, std::integral_constant<int, 0x142>{}));  // lane 15 of the 16 before
+}
+__device__ __forceinline__ uint32_t pa_exponent(float v) { return __float_as_uint(v) & 0x7f800000u; }
+
 // LDS of one buffer: K [terms][KT][HD + 8] and V^T [terms][HD][KT + 8] halves, then (block-scaled rows) the score factors and
-// the normalised value scales [KT] and the value reference of the tile.  Both row strides are 4 banks modulo 16, which keeps
+// the normalised value scales [KT] and the value references of every 32 rows.  Both row strides are 4 banks modulo 16, which keeps
 // the 16-byte fragment reads free of conflicts; the 16-byte pieces of a V^T row are permuted by the row's 16-row group so that the
 // transposing 8-byte stores of a wavefront spread over all banks.
 template <int HD, bool I16, int NW>
@@ -73,8 +88,10 @@ struct PaTile {
 // probabilities and -- when q_lo is given -- the queries: each of the two products of a tile becomes three matrix
 // instructions (hi x hi, lo x hi, hi x lo; lo x lo is below fp32 resolution) and no operand carries a single half rounding.
 // A probability is multiplied with its row's value scale before it is split; so that the product stays in the normal range of a
-// half, scales are taken relative to a power of two, the one at or below the largest scale up to the tile at hand (the reference, part
-// of the online rescale).
+// half, scales are taken relative to a power of two, the one at or below the largest scale up to the 32 rows at hand (the reference,
+// part of the online rescale).  The grid of the low term is 2^-25 of a probability for rows of 2^-14 of the reference and larger, the
+// grid that probabilities split by themselves would have; below that a row loses one bit per factor of two.  Rows that a query does not
+// see have no part in its reference: in the diagonal block every query takes its own, as a shift of its running maximum.
 // q_lo (optional, I16 only): second half term of q, laid out like q.
 // out_lo (optional): half(o - half(o)), the second term of the output for a two-term output projection.
 // xcd_heads > 0: heads of all sequences, a multiple of 8; the workgroups of one head and of its neighbours run on one XCD, whose
@@ -219,15 +236,18 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
         }
         if (I16 && w == 0) {
             float *sc = reinterpret_cast<float *>(vs + L::V_HALVES);
-            vmax_run = fmaxf(vmax_run, wave_max(vscr < INFINITY ? vscr : 0.f));
+            const float m = pa_max32(fabsf(vscr) < INFINITY ? fabsf(vscr) : 0.f);
+            const float top0 = fmaxf(vmax_run, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(m), 31)));
+            vmax_run = fmaxf(top0, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(m), 63)));
+            const float top = lane < 32 ? top0 : vmax_run;
             // the power of two at or below the largest scale: taking it out is exact
-            const float ref = vmax_run > 0.f ? fmaxf(__uint_as_float(__float_as_uint(vmax_run) & 0x7f800000u), 1.17549435e-38f) : 0.f;
+            const float ref = top > 0.f ? fmaxf(__uint_as_float(pa_exponent(top)), 1.17549435e-38f) : 0.f;
             if (lane < KT) {
                 sc[lane] = kscr * (64.f * c2);
                 // below 2 PA_PSCALE by construction; the clamp keeps a row of infinities from reaching queries that do not see it
-                sc[KT + lane] = ref > 0.f ? fminf(ldexpf(vscr, PA_PSHIFT - ilogbf(ref)), 2.f * PA_PSCALE) : 0.f;
+                sc[KT + lane] = ref > 0.f ? fminf(ldexpf(vscr, PA_PSHIFT + 127 - (int)(__float_as_uint(ref) >> 23)), 2.f * PA_PSCALE) : 0.f;
             }
-            if (lane == 0) sc[2 * KT] = ref;
+            if (lane < KT && (lane & 31) == 0) sc[2 * KT + (lane >> 5) * 2] = ref;
         }
     };
 
@@ -263,8 +283,9 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
             }
             if (I16) sacc += slow;
             // register i holds key row (i/4)*8 + half*4 + (i%4) of the block, query column l32
+            const float *blk = sc + 2 * KT + sub * 2;
             float rel = 1.f, vnew = 0.f;
-            if (I16) vnew = sc[2 * KT];
+            if (I16) vnew = blk[0];
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
                 f32x4_t f = {c2, c2, c2, c2};
@@ -272,17 +293,34 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
 #pragma unroll
                 for (int j = 0; j < 4; ++j) sacc[i4 * 4 + j] *= f[j];
             }
-            if (key0 + 31 > q0) {  // the diagonal block: causal mask
+            const bool diagonal = key0 == q0;
+            float seen = 0.f;  // largest normalised value scale among the rows of the block that this query sees
+            if (diagonal) {    // causal mask
 #pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    if (key0 + (i >> 2) * 8 + half * 4 + (i & 3) > qpos) sacc[i] = -INFINITY;
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    f32x4_t f = {0.f, 0.f, 0.f, 0.f};
+                    if (I16) f = *reinterpret_cast<const f32x4_t *>(sc + KT + sub * 32 + i4 * 8 + half * 4);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (key0 + i4 * 8 + half * 4 + j > qpos) sacc[i4 * 4 + j] = -INFINITY;
+                        else if (I16) seen = fmaxf(seen, fabsf(f[j]));
+                    }
+                }
             }
             float tmax = sacc[0];
 #pragma unroll
             for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, sacc[i]);
             tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-            const float mnew = fmaxf(mrun, tmax);  // finite: key 0 is visible to every query
+            float mnew = fmaxf(mrun, tmax);  // finite: key 0 is visible to every query
             if (I16 && vnew != vref) rel = vref / vnew;  // powers of two; the reference only grows, so it is positive here
+            if (I16 && diagonal) {
+                // The query's own reference, the largest of the rows that it sees, may be 2^k below the block's: its probabilities are
+                // taken 2^k times larger, in numerator and denominator (this block is the query's last).
+                seen = fmaxf(seen, __shfl_xor(seen, 32, 64));
+                const float own = fmaxf(vref, __uint_as_float(pa_exponent(seen)) * (vnew * (1.f / PA_PSCALE)));
+                const int shift = (int)(__float_as_uint(vnew) >> 23) - (int)(__float_as_uint(own) >> 23);
+                if (own > 0.f) mnew -= (float)(shift < 100 ? shift : 100);
+            }
             if (__any(mnew != mrun) || rel != 1.f) {
                 const float alpha = __builtin_amdgcn_exp2f(mrun - mnew);
                 lrun *= alpha;

@@ -1033,6 +1033,61 @@ def test_prefill_attention_two_term_error_against_64_bits(ops, hd, T):
     assert np.sqrt(err / ref2) < 1e-6, np.sqrt(err / ref2)
 
 
+def _two_term_prefill(ops, hd, T, kscale, vscale, kc, vc, seed):
+    """Rows of one sequence of 4 heads; returns what attention stored in its two terms and the queries, in fp64."""
+    H, S = kc.shape[1], kc.shape[2]
+    qf = randn_f32((T, H * hd), seed, std=1.5)
+    q = qf.to(torch.float16)
+    q_lo = (qf - q.float()).to(torch.float16)
+    out = torch.zeros((T, H * hd), dtype=torch.float16, device=DEV)
+    out_lo = torch.zeros_like(out)
+    ops.prefill_attention(q, kc, vc, out, 1, 0, T, H, H, hd, S, kscale=kscale, vscale=vscale, out_lo=out_lo, q_lo=q_lo)
+    torch.cuda.synchronize()
+    return (np64(out) + np64(out_lo)).reshape(T, H, hd), (np64(q) + np64(q_lo)).reshape(T, H, hd), np64(out).reshape(T, H, hd)
+
+
+def _attention_error(got, qn, kn, vn, rows):
+    err = ref2 = 0.0
+    for u in range(kn.shape[1]):
+        for i in rows:
+            ref = orc.attend(qn[i, u], kn[0, u, : i + 1], vn[0, u, : i + 1])
+            err += ((got[i, u] - ref) ** 2).sum()
+            ref2 += (ref ** 2).sum()
+    return np.sqrt(err / ref2)
+
+
+# rows at both ends of a 32-row block, in the second block of a 64-row tile, and past a tile
+@pytest.mark.parametrize("hd,T,at", [(128, 100, 31), (128, 100, 40), (128, 300, 40), (128, 300, 95), (64, 300, 130), (64, 60, 20)])
+@pytest.mark.parametrize("k", [3, 12, 20, 60])
+def test_prefill_attention_is_causal_in_the_value_scales(ops, hd, T, at, k):
+    """A row whose value scale is 2^k times the others' leaves the queries before it as exact as without it: the error against 64 bits stays
+    below the 1e-6 of the two-term output."""
+    H, S = 4, T + 5
+    kc, ks, kn = _random_block_scaled((1, H, S, hd), 205)
+    vc, vs, _ = _random_block_scaled((1, H, S, hd), 206)
+    vs[:, :, at] *= 2.0 ** k
+    vn = np64(vc) * np64(vs)[..., None]
+    got, qn, _ = _two_term_prefill(ops, hd, T, ks, vs, kc, vc, 207)
+    assert _attention_error(got, qn, kn, vn, range(at)) < 1e-6
+
+
+@pytest.mark.parametrize("hd,T", [(128, 100), (128, 300), (64, 200)])
+def test_prefill_attention_value_scales_zero_negative_and_far_apart(ops, hd, T):
+    """No row of the first 70 (a tile and a bit) has a value scale, some later ones are negative, and they spread over 2^13: within the
+    14 bits by which a scale may lie below the reference at no loss."""
+    H, S = 4, T + 5
+    kc, ks, kn = _random_block_scaled((1, H, S, hd), 205)
+    vc, vs, _ = _random_block_scaled((1, H, S, hd), 206)
+    vs[:, :, :70] = 0.0
+    vs *= 2.0 ** torch.randint(-13, 1, (S,), generator=torch.Generator().manual_seed(208)).float().to(DEV)
+    vs[:, :, 75::9] *= -1.0
+    vs = vs.contiguous()
+    vn = np64(vc) * np64(vs)[..., None]
+    got, qn, _ = _two_term_prefill(ops, hd, T, ks, vs, kc, vc, 207)
+    assert (got[:70] == 0).all()
+    assert _attention_error(got, qn, kn, vn, range(70, T)) < 1e-6
+
+
 @pytest.mark.parametrize("M", [1, 32, 33, 64, 65, 129])
 @pytest.mark.parametrize("K,splits", [(128, 1), (520, 1), (1160, 2), (1664, 3), (640, 1)])
 def test_gemm_skinny_row_tiles(ops, M, K, splits):
