@@ -69,7 +69,7 @@ __device__ __forceinline__ float pa_max32(float v) {
 __device__ __forceinline__ uint32_t pa_exponent(float v) { return __float_as_uint(v) & 0x7f800000u; }
 
 // LDS of one buffer: K [terms][KT][HD + 8] and V^T [terms][HD][KT + 8] halves, then (block-scaled rows) the score factors and
-// the normalised value scales [KT] and the value references of every 32 rows.  Both row strides are 4 banks modulo 16, which keeps
+// the normalised value scales [KT] and of every 32 rows the value reference and the mask of rows without a finite scale.  Both row strides are 4 banks modulo 16, which keeps
 // the 16-byte fragment reads free of conflicts; the 16-byte pieces of a V^T row are permuted by the row's 16-row group so that the
 // transposing 8-byte stores of a wavefront spread over all banks.
 template <int HD, bool I16, int NW>
@@ -92,6 +92,7 @@ struct PaTile {
 // part of the online rescale).  The grid of the low term is 2^-25 of a probability for rows of 2^-14 of the reference and larger, the
 // grid that probabilities split by themselves would have; below that a row loses one bit per factor of two.  Rows that a query does not
 // see have no part in its reference: in the diagonal block every query takes its own, as a shift of its running maximum.
+// A row whose value scale is not finite makes the output of the queries that see it NaN (stored as the largest half, like any NaN).
 // q_lo (optional, I16 only): second half term of q, laid out like q.
 // out_lo (optional): half(o - half(o)), the second term of the output for a two-term output projection.
 // xcd_heads > 0: heads of all sequences, a multiple of 8; the workgroups of one head and of its neighbours run on one XCD, whose
@@ -236,18 +237,23 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
         }
         if (I16 && w == 0) {
             float *sc = reinterpret_cast<float *>(vs + L::V_HALVES);
-            const float m = pa_max32(fabsf(vscr) < INFINITY ? fabsf(vscr) : 0.f);
+            const bool finite = fabsf(vscr) < INFINITY;  // not for a NaN
+            const float m = pa_max32(finite ? fabsf(vscr) : 0.f);
             const float top0 = fmaxf(vmax_run, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(m), 31)));
             vmax_run = fmaxf(top0, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(m), 63)));
             const float top = lane < 32 ? top0 : vmax_run;
             // the power of two at or below the largest scale: taking it out is exact
             const float ref = top > 0.f ? fmaxf(__uint_as_float(pa_exponent(top)), 1.17549435e-38f) : 0.f;
+            const uint64_t bad = __ballot(!finite);
             if (lane < KT) {
                 sc[lane] = kscr * (64.f * c2);
-                // below 2 PA_PSCALE by construction; the clamp keeps a row of infinities from reaching queries that do not see it
-                sc[KT + lane] = ref > 0.f ? fminf(ldexpf(vscr, PA_PSHIFT + 127 - (int)(__float_as_uint(ref) >> 23)), 2.f * PA_PSCALE) : 0.f;
+                sc[KT + lane] = finite && ref > 0.f ? ldexpf(vscr, PA_PSHIFT + 127 - (int)(__float_as_uint(ref) >> 23)) : 0.f;
             }
-            if (lane < KT && (lane & 31) == 0) sc[2 * KT + (lane >> 5) * 2] = ref;
+            if (lane < KT && (lane & 31) == 0) {
+                float *blk = sc + 2 * KT + (lane >> 5) * 2;
+                blk[0] = ref;
+                reinterpret_cast<uint32_t *>(blk)[1] = (uint32_t)(bad >> lane);
+            }
         }
     };
 
@@ -320,6 +326,10 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
                 const float own = fmaxf(vref, __uint_as_float(pa_exponent(seen)) * (vnew * (1.f / PA_PSCALE)));
                 const int shift = (int)(__float_as_uint(vnew) >> 23) - (int)(__float_as_uint(own) >> 23);
                 if (own > 0.f) mnew -= (float)(shift < 100 ? shift : 100);
+            }
+            if (I16) {  // rows without a finite value scale
+                const uint32_t bad = reinterpret_cast<const uint32_t *>(blk)[1];
+                if (bad & (diagonal ? (2u << l32) - 1u : ~0u)) lrun = __builtin_nanf("");
             }
             if (__any(mnew != mrun) || rel != 1.f) {
                 const float alpha = __builtin_amdgcn_exp2f(mrun - mnew);

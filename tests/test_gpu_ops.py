@@ -1071,6 +1071,21 @@ def test_prefill_attention_is_causal_in_the_value_scales(ops, hd, T, at, k):
     assert _attention_error(got, qn, kn, vn, range(at)) < 1e-6
 
 
+@pytest.mark.parametrize("hd,T,at", [(128, 100, 40), (128, 300, 95), (64, 300, 130)])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_prefill_attention_value_scale_that_is_not_finite(ops, hd, T, at, bad):
+    """The queries that see the row are not finite (a NaN is stored as minus the largest half), the others keep their bits."""
+    H, S = 4, T + 5
+    kc, ks, _ = _random_block_scaled((1, H, S, hd), 205)
+    vc, vs, _ = _random_block_scaled((1, H, S, hd), 206)
+    vs[:, 1:, at] = 0.0   # heads 1 and on: the same row, once without a share in the output, once not finite
+    plain, _, _ = _two_term_prefill(ops, hd, T, ks, vs, kc, vc, 207)
+    vs[:, 1:, at] = bad
+    got, _, hi = _two_term_prefill(ops, hd, T, ks, vs, kc, vc, 207)
+    assert (got[:at] == plain[:at]).all() and (got[:, 0] == plain[:, 0]).all()
+    assert (hi[at:, 1:] == -65504).all()
+
+
 @pytest.mark.parametrize("hd,T", [(128, 100), (128, 300), (64, 200)])
 def test_prefill_attention_value_scales_zero_negative_and_far_apart(ops, hd, T):
     """No row of the first 70 (a tile and a bit) has a value scale, some later ones are negative, and they spread over 2^13: within the
