@@ -14,14 +14,20 @@
 //     fragment is one 16-byte LDS read.
 // Softmax and accumulation are fp32; probabilities are rounded to half for the matrix cores (two terms over block-scaled rows).
 //
-// What bounds it: long prompts the matrix cores together with the vector work of the softmax (691-853 TFLOP/s executed at 2048 and
-// 4096 positions); short ones the chain fetch -> convert -> barrier of their few tiles.  A version with 128 queries per workgroup,
-// 16-bit gathers from untransposed V (128 LDS reads per 32 keys and wavefront instead of 16), a single buffer and every element
-// scaled in fp32 on its way to LDS kept the matrix cores 10 % busy.  us a launch, that version -> this one, block-scaled rows, 32
-// heads: 8 x 2048 positions 3516 -> 1203, 32 x 512 997 -> 483, 32 x 384 467 -> 316, 37 x 205 288 -> 182, 128 x 128 380 -> 265,
-// 1 x 128 18 -> 19; half rows, 32/8 heads, 16 x 1024 682 -> 426.
-// Error of the two-term output against 64 bits (normal rows, scores of deviation 1.5, before -> now): 128 keys 3.05e-7 -> 2.27e-7,
-// 333 keys 3.67e-7 -> 2.76e-7, 1000 keys 4.61e-7 -> 3.49e-7; scores all equal 1.82e-7 -> 1.85e-7.
+// What bounds it: long prompts the matrix cores together with the vector work of the softmax (719-886 TFLOP/s executed at 2048 and
+// 4096 positions); short ones the chain of latencies of a wavefront's tiles: of 6500 cycles per 32 keys with one wavefront per SIMD, 2000
+// are the two products, 1700 the softmax, 1300 the conversion to LDS.  What keeps the rest of that chain short:
+//   * consecutive rows are read through descriptors (one address register per operand and no comparison; rows of page lists, and
+//     sequences beyond 32-bit offsets, by a general path: template parameter LINEAR);
+//   * K and V fragments are read one product ahead; the queries are requested behind the first tile and arrive while it is staged;
+//   * there is no barrier after the last tile, so the wavefronts above its diagonal store their rows while the others multiply.
+//   Without these three: one prompt of 64 / 128 / 256 positions, 32 heads, block-scaled rows 12.6 / 20.4 / 33.4 us, now 10.4 / 16.7 / 28.3.
+// Compared with 128 queries per workgroup, 16-bit gathers from untransposed V (128 LDS reads per 32 keys and wavefront instead of 16), a
+// single buffer and every element scaled in fp32 on its way to LDS, us a launch, that -> now, block-scaled rows, 32 heads: 8 x 2048
+// positions 3530 -> 1150, 32 x 512 1000 -> 440, 32 x 384 465 -> 284, 37 x 205 288 -> 174, 128 x 128 380 -> 244, 1 x 1000 118 -> 84, 1 x 128
+// 17.8 -> 15.6; half rows, 32/8 heads, 16 x 1024 681 -> 411.
+// Error of the two-term output against 64 bits (normal rows, scores of deviation 1.5, that -> now): 128 keys 3.05e-7 -> 2.27e-7,
+// 333 keys 3.67e-7 -> 2.76e-7, 1000 keys 4.61e-7 -> 3.49e-7; scores all equal 1.82e-7 -> 1.85e-7, and all scales equal as well 1.82e-7 -> 2.02e-7.
 #include <type_traits>
 
 #include "kernels.h"
@@ -44,10 +50,11 @@ __device__ __forceinline__ void pa_split_i16x2(uint32_t n, uint32_t &hi, uint32_
     lo = __builtin_bit_cast(uint32_t, b - (s - a));
 }
 
-// 4 rows x 4 columns of 16-bit values (two packed words per row) -> the 4 columns, 4 rows each
-__device__ __forceinline__ void pa_transpose4(const u32x2_t (&r)[4], u32x2_t (&c)[4]) {
+// 4 rows x 2 W columns of 16-bit values (W packed words per row) -> the columns, 4 rows each
+template <int W>
+__device__ __forceinline__ void pa_transpose4(const uint32_t (&r)[4][W], u32x2_t (&c)[2 * W]) {
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
+    for (int p = 0; p < W; ++p) {
         c[2 * p].x = __builtin_amdgcn_perm(r[1][p], r[0][p], 0x05040100u);
         c[2 * p].y = __builtin_amdgcn_perm(r[3][p], r[2][p], 0x05040100u);
         c[2 * p + 1].x = __builtin_amdgcn_perm(r[1][p], r[0][p], 0x07060302u);
@@ -78,9 +85,8 @@ struct PaTile {
     static constexpr int KSTR = HD + 8, VSTR = KT + 8;
     static constexpr int K_HALVES = NT * KT * KSTR, V_HALVES = NT * HD * VSTR;
     static constexpr int BYTES = (K_HALVES + V_HALVES) * 2 + (I16 ? (2 * KT + 4) * 4 : 0);
-    __device__ static __forceinline__ int v_at(int term, int dim, int piece) {
-        return (term * HD + dim) * VSTR + ((piece ^ (dim >> 4)) & (KT / 8 - 1)) * 8;
-    }
+    // piece p (keys 8 p .. + 7) of row dim is kept in place p ^ (dim / 16) of the row, modulo the KT / 8 pieces
+    __device__ static __forceinline__ int v_place(int piece, int dim) { return ((piece ^ (dim >> 4)) & (KT / 8 - 1)) * 8; }
 };
 
 // I16: the cache rows are 16-bit block-scaled fixed point (KvMap::kscale / vscale).  A row element has more
@@ -97,7 +103,7 @@ struct PaTile {
 // out_lo (optional): half(o - half(o)), the second term of the output for a two-term output projection.
 // xcd_heads > 0: heads of all sequences, a multiple of 8; the workgroups of one head and of its neighbours run on one XCD, whose
 // L2 then reads their cache rows once.
-template <int HD, bool I16, int NW>
+template <int HD, bool I16, int NW, bool LINEAR>
 __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16_t *__restrict__ q, const f16_t *__restrict__ q_lo,
                                                                        const f16_t *__restrict__ kc, const f16_t *__restrict__ vc,
                                                                        f16_t *__restrict__ out, f16_t *__restrict__ out_lo, int b0,
@@ -124,20 +130,6 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
     const int qpos = q0 + l32;          // this lane's query column
     const size_t ldq = (size_t)Hq * HD;
 
-    // Q fragments (B operand of S^T = K Q^T): lane = (query column l32, hd slice half*8 + 16*s)
-    f16x8_t qf[KS], ql[I16 ? KS : 1];
-    const bool two_q = I16 && q_lo != nullptr;  // uniform
-    {
-        int qrow = qpos < T ? qpos : T - 1;
-        const size_t qoff = ((size_t)bl * T + qrow) * ldq + (size_t)u * HD + half * 8;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) qf[s] = *reinterpret_cast<const f16x8_t *>(q + qoff + s * 16);
-        if (I16) {
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-                ql[s] = two_q ? *reinterpret_cast<const f16x8_t *>(q_lo + qoff + s * 16) : f16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
-        }
-    }
     int n_keys = T;  // keys this sequence really has in the cache
     if (d_valid) {
         int nv = d_valid[b0 + bl];
@@ -153,12 +145,40 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
     float vref = 0.f;                    // value reference the accumulators are relative to
     const float c2 = rsqrtf((float)HD) * 1.44269504088896340736f;  // scores times this are exponents of 2
 
-    // ---- staging: K as rows (16-byte pieces), V as groups of 4 rows x 4 columns, the scales by the first KT threads (wavefront 0)
-    constexpr int VG = (KT / 4) * (HD / 4);  // 4 x 4 groups of a tile (one per thread at most)
+    // ---- staging: K as rows (16-byte pieces), V as groups of 4 rows x HD / 32 columns, one per thread, the scales by the first KT
+    //      threads (wavefront 0)
+    constexpr int VW = HD / 64;  // words of 2 columns
+    const int vrow = t / 32 * 4, vcol = t % 32 * (2 * VW);
     u32x4_t kreg[KP];
-    u32x2_t vreg[4];
+    uint32_t vreg[4][VW];
     float kscr = 0.f, vscr = 0.f, vmax_run = 0.f;
+    // LINEAR: the keys of a sequence are consecutive rows.  The descriptors end with its last key, so rows that it does not have read as
+    // zeros, and a tile takes three address registers and no comparison.
+    const size_t slab = LINEAR ? ((size_t)(b0 + bl) * Hkv + kvh) * S : 0;
+    auto rsrc = [&](const void *p, int row_bytes) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, LINEAR ? n_keys * row_bytes : 0, 0x00020000);
+    };
+    const __amdgpu_buffer_rsrc_t kr = rsrc(kc + slab * HD, HD * 2), vr = rsrc(vc + slab * HD, HD * 2);
+    const __amdgpu_buffer_rsrc_t ksr = rsrc(I16 ? map.kscale + slab : nullptr, 4), vsr = rsrc(I16 ? map.vscale + slab : nullptr, 4);
     auto fetch = [&](int kt) {
+        if constexpr (LINEAR) {
+#pragma unroll
+            for (int i = 0; i < KP; ++i) kreg[i] = __builtin_amdgcn_raw_buffer_load_b128(kr, t * 16 + (kt * KP + i) * THREADS * 16, 0, 0);
+            const int vat = ((kt * KT + vrow) * HD + vcol) * 2;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if constexpr (VW == 2) {
+                    const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(vr, vat + r * HD * 2, 0, 0);
+                    vreg[r][0] = v.x; vreg[r][1] = v.y;
+                } else vreg[r][0] = __builtin_amdgcn_raw_buffer_load_b32(vr, vat + r * HD * 2, 0, 0);
+            }
+            if (I16 && w == 0) {
+                const int at = lane < KT ? (kt * KT + lane) * 4 : 0x7fffff00;  // the lanes behind a tile of 32 rows: out of range
+                kscr = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ksr, at, 0, 0));
+                vscr = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vsr, at, 0, 0));
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < KP; ++i) {
             const int idx = t + i * THREADS, key = kt * KT + idx / (HD / 8);
@@ -166,14 +186,21 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
             if (key < n_keys)  // rows past the prompt may hold arbitrary bits: keep them out (0 * NaN)
                 kreg[i] = *reinterpret_cast<const u32x4_t *>(kc + kv_row_index(map, b0 + bl, kvh, Hkv, S, key) * HD + (idx % (HD / 8)) * 8);
         }
-        const int key4 = kt * KT + t / (HD / 4) * 4;
+        const int key4 = kt * KT + vrow;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) vreg[r] = u32x2_t{0u, 0u};
-        if (t < VG && key4 < n_keys) {  // 4 aligned rows share a page (a page holds a power of two >= 16)
-            const f16_t *vp = vc + kv_row_index(map, b0 + bl, kvh, Hkv, S, key4) * HD + (t % (HD / 4)) * 4;
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int p = 0; p < VW; ++p) vreg[r][p] = 0u;
+        if (key4 < n_keys) {  // 4 aligned rows share a page (a page holds a power of two >= 16)
+            const f16_t *vp = vc + kv_row_index(map, b0 + bl, kvh, Hkv, S, key4) * HD + vcol;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (key4 + r < n_keys) vreg[r] = *reinterpret_cast<const u32x2_t *>(vp + r * HD);
+                if (key4 + r < n_keys) {
+                    if constexpr (VW == 2) {
+                        const u32x2_t v = *reinterpret_cast<const u32x2_t *>(vp + r * HD);
+                        vreg[r][0] = v.x; vreg[r][1] = v.y;
+                    } else vreg[r][0] = *reinterpret_cast<const uint32_t *>(vp + r * HD);
+                }
         }
         if (I16 && w == 0) {
             const int key = kt * KT + lane;
@@ -207,33 +234,26 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
                 *reinterpret_cast<u32x4_t *>(at) = kreg[i];
             }
         }
-        if (t < VG) {
-            // rows 8a + 4h + 0..3 of a 32-row block are slots 4 (a & 1) + 0..3 of the fragment (step a / 2, half-wavefront h)
-            const int g = t / (HD / 4), dim = (t % (HD / 4)) * 4;
-            const int piece = (g >> 3) * 4 + ((g >> 2) & 1) * 2 + (g & 1), slot = ((g >> 1) & 1) * 4;
-            u32x2_t col[4], low[4];
-            if (I16) {
-                u32x2_t hi[4];
+        // rows 8a + 4h + 0..3 of a 32-row block are slots 4 (a & 1) + 0..3 of the fragment (step a / 2, half-wavefront h)
+        const int g = vrow / 4, piece = (g >> 3) * 4 + ((g >> 2) & 1) * 2 + (g & 1), slot = ((g >> 1) & 1) * 4;
+        f16_t *at = vs + vcol * L::VSTR + L::v_place(piece, vcol) + slot;  // of the group's first column; all its columns have one place
+        u32x2_t col[2 * VW];
+        if (I16) {
+            uint32_t hi[4][VW], low[4][VW];
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        uint32_t h, l;
-                        pa_split_i16x2(vreg[r][p], h, l);
-                        hi[r][p] = h;
-                        low[r][p] = l;
-                    }
-                pa_transpose4(hi, col);
+                for (int p = 0; p < VW; ++p) pa_split_i16x2(vreg[r][p], hi[r][p], low[r][p]);
+            pa_transpose4(hi, col);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x2_t *>(vs + L::v_at(0, dim + i, piece) + slot) = col[i];
-                pa_transpose4(low, col);
+            for (int i = 0; i < 2 * VW; ++i) *reinterpret_cast<u32x2_t *>(at + i * L::VSTR) = col[i];
+            pa_transpose4(low, col);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x2_t *>(vs + L::v_at(1, dim + i, piece) + slot) = col[i];
-            } else {
-                pa_transpose4(vreg, col);
+            for (int i = 0; i < 2 * VW; ++i) *reinterpret_cast<u32x2_t *>(at + (HD + i) * L::VSTR) = col[i];
+        } else {
+            pa_transpose4(vreg, col);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x2_t *>(vs + L::v_at(0, dim + i, piece) + slot) = col[i];
-            }
+            for (int i = 0; i < 2 * VW; ++i) *reinterpret_cast<u32x2_t *>(at + i * L::VSTR) = col[i];
         }
         if (I16 && w == 0) {
             float *sc = reinterpret_cast<float *>(vs + L::V_HALVES);
@@ -261,6 +281,20 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
     if (last_q > T - 1) last_q = T - 1;
     const int n_tiles = last_q / KT + 1;  // key tiles any wavefront of the workgroup needs
     fetch(0);
+    // Q fragments (B operand of S^T = K Q^T): lane = (query column l32, hd slice half*8 + 16*s); on their way while the first tile is staged
+    f16x8_t qf[KS], ql[I16 ? KS : 1];
+    const bool two_q = I16 && q_lo != nullptr;  // uniform
+    {
+        const int qrow = qpos < T ? qpos : T - 1;
+        const size_t qoff = ((size_t)bl * T + qrow) * ldq + (size_t)u * HD + half * 8;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qf[s] = *reinterpret_cast<const f16x8_t *>(q + qoff + s * 16);
+        if (I16) {
+            const f16_t *qp = two_q ? q_lo : q;  // without a second term: not used
+#pragma unroll
+            for (int s = 0; s < KS; ++s) ql[s] = *reinterpret_cast<const f16x8_t *>(qp + qoff + s * 16);
+        }
+    }
     stash(0);
     __syncthreads();
     for (int kt = 0; kt < n_tiles; ++kt) {
@@ -277,16 +311,27 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
             f32x16_t sacc, slow;
 #pragma unroll
             for (int i = 0; i < 16; ++i) sacc[i] = slow[i] = 0.f;
+            // fragments are read one k-step ahead of their products
+            auto scores = [&](auto two_tag) {
+                f16x8_t kf[2][NT];
+                auto read_k = [&](int s) {
 #pragma unroll
-            for (int s = 0; s < KS; ++s) {
+                    for (int tm = 0; tm < NT; ++tm)
+                        kf[s & 1][tm] = *reinterpret_cast<const f16x8_t *>(ks + (tm * KT + sub * 32 + l32) * L::KSTR + half * 8 + s * 16);
+                };
+                read_k(0);
 #pragma unroll
-                for (int tm = 0; tm < NT; ++tm) {
-                    f16x8_t kf = *reinterpret_cast<const f16x8_t *>(ks + (tm * KT + sub * 32 + l32) * L::KSTR + half * 8 + s * 16);
-                    if (tm == 0) sacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[s], sacc, 0, 0, 0);
-                    else slow = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[s], slow, 0, 0, 0);
-                    if (I16 && tm == 0 && two_q) slow = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, ql[s], slow, 0, 0, 0);
+                for (int s = 0; s < KS; ++s) {
+                    if (s + 1 < KS) read_k(s + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    sacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[s & 1][0], qf[s], sacc, 0, 0, 0);
+                    if (decltype(two_tag)::value) slow = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[s & 1][0], ql[I16 ? s : 0], slow, 0, 0, 0);
+                    if (I16) slow = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[s & 1][NT - 1], qf[s], slow, 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-            }
+            };
+            if (I16 && two_q) scores(std::true_type{});
+            else scores(std::false_type{});
             if (I16) sacc += slow;
             // register i holds key row (i/4)*8 + half*4 + (i%4) of the block, query column l32
             const float *blk = sc + 2 * KT + sub * 2;
@@ -341,6 +386,16 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
                 mrun = mnew;
                 vref = vnew;
             }
+            f16x8_t vf[2][NT];  // V^T fragments, read one product ahead
+            // place of piece 4 sub + 2 s + half of row 32 e + l32, bit by bit: what depends on the lane is one address
+            auto read_v = [&](int n) {
+                const int s = n / ET, e = n % ET;
+                const f16_t *at = vs + l32 * L::VSTR + (half ^ (l32 >> 4)) * 8 + (KT == 64 ? (sub ^ (e >> 1)) * 32 : 0);
+#pragma unroll
+                for (int tm = 0; tm < NT; ++tm)
+                    vf[n & 1][tm] = *reinterpret_cast<const f16x8_t *>(at + (tm * HD + e * 32) * L::VSTR + (s ^ (e & 1)) * 16);
+            };
+            read_v(0);
             f16x8_t pf[2], pl[I16 ? 2 : 1];
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
@@ -366,19 +421,20 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
             // O^T += V^T P^T.  Slot j of k-step s in lane-half h stands for key (2s + j/4)*8 + h*4 + j%4 -- the
             // key that accumulator register s*8 + j already holds, so P needs no data movement.
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {
-#pragma unroll
-                for (int e = 0; e < ET; ++e) {
-#pragma unroll
-                    for (int tm = 0; tm < NT; ++tm) {
-                        f16x8_t vf = *reinterpret_cast<const f16x8_t *>(vs + L::v_at(tm, e * 32 + l32, sub * 4 + s * 2 + half));
-                        oacc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf[s], oacc[e], 0, 0, 0);
-                        if (I16 && tm == 0) oacc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pl[s], oacc[e], 0, 0, 0);
-                    }
+            for (int n = 0; n < 2 * ET; ++n) {
+                const int s = n / ET, e = n % ET;
+                if (n + 1 < 2 * ET) read_v(n + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                oacc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[n & 1][0], pf[s], oacc[e], 0, 0, 0);
+                if (I16) {
+                    oacc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[n & 1][0], pl[s], oacc[e], 0, 0, 0);
+                    oacc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[n & 1][NT - 1], pf[s], oacc[e], 0, 0, 0);
                 }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (more) stash((kt + 1) & 1);  // the buffer of tile kt - 1: read before the last barrier
+        if (!more) break;    // the wavefronts above the diagonal of the last tile store their rows while the others multiply
+        stash((kt + 1) & 1);  // the buffer of tile kt - 1: read before the last barrier
         __syncthreads();
     }
 
@@ -405,18 +461,19 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_attention_kernel(const f16
     }
 }
 
-template <int HD, bool I16, int NW>
+template <int HD, bool I16, int NW, bool LINEAR>
 static void launch_pa(const f16_t *q, const f16_t *q_lo, const f16_t *kc, const f16_t *vc, f16_t *out, f16_t *out_lo, int nb, int b0,
                       int T, int Hq, int Hkv, int S, const KvMap &map, const int32_t *d_valid, hipStream_t st) {
     constexpr int lds = 2 * PaTile<HD, I16, NW>::BYTES;
     static_assert(lds <= 160 * 1024, "two buffers fit a compute unit");
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_attention_kernel<HD, I16, NW>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_attention_kernel<HD, I16, NW, LINEAR>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     (void)attr;
     dim3 grid(ceil_div(T, 32 * NW), Hq, nb);
     const int64_t heads = (int64_t)Hq * nb;
     const int xcd_heads = heads % 8 == 0 && heads * grid.x < (1ll << 31) ? (int)heads : 0;
-    prefill_attention_kernel<HD, I16, NW><<<grid, 64 * NW, lds, st>>>(q, q_lo, kc, vc, out, out_lo, b0, T, Hq, Hkv, S, map, d_valid, xcd_heads);
+    prefill_attention_kernel<HD, I16, NW, LINEAR><<<grid, 64 * NW, lds, st>>>(q, q_lo, kc, vc, out, out_lo, b0, T, Hq, Hkv, S, map, d_valid,
+                                                                              xcd_heads);
 }
 
 void launch_prefill_attention(const f16_t *q, const f16_t *kc, const f16_t *vc, f16_t *out, int nb, int b0, int T,
@@ -424,13 +481,25 @@ void launch_prefill_attention(const f16_t *q, const f16_t *kc, const f16_t *vc, 
                               const f16_t *q_lo) {
     if (nb <= 0 || T <= 0) return;
     const bool i16 = map.kscale != nullptr;
-    const bool wide = T > 128;  // up to 128 positions the second half of a wide workgroup would hold no query
+    // 256 queries per workgroup from 129 positions on; up to 128 its second half would hold no query.  128 / 256 queries, time ratio, 1-4
+    // prompts, 32-64 heads of 128: up to 256 positions 0.87-0.94, 384 1.17-1.38, 512 0.95-1.20, 1024 0.97-1.22, 2048 0.96-1.21, 4096 0.98-1.07;
+    // 16 prompts 0.83-1.11.
+    const bool wide = T > 128;
+    const bool linear = !map.table && (int64_t)T * hd * 2 < (1ll << 30);  // 32-bit offsets inside a sequence
     auto run = [&](auto kernel) { kernel(q, i16 ? q_lo : nullptr, kc, vc, out, out_lo, nb, b0, T, Hq, Hkv, S, map, d_valid, st); };
-    if (hd == 128) {
-        if (i16) wide ? run(launch_pa<128, true, 8>) : run(launch_pa<128, true, 4>);
-        else wide ? run(launch_pa<128, false, 8>) : run(launch_pa<128, false, 4>);
-    } else {
-        if (i16) wide ? run(launch_pa<64, true, 8>) : run(launch_pa<64, true, 4>);
-        else wide ? run(launch_pa<64, false, 8>) : run(launch_pa<64, false, 4>);
-    }
+    auto rows = [&](auto hd_tag, auto i16_tag, auto nw_tag) {
+        constexpr int HD = decltype(hd_tag)::value, NW = decltype(nw_tag)::value;
+        constexpr bool I16 = decltype(i16_tag)::value;
+        linear ? run(launch_pa<HD, I16, NW, true>) : run(launch_pa<HD, I16, NW, false>);
+    };
+    auto width = [&](auto hd_tag, auto i16_tag) {
+        if (wide) rows(hd_tag, i16_tag, std::integral_constant<int, 8>{});
+        else rows(hd_tag, i16_tag, std::integral_constant<int, 4>{});
+    };
+    auto type = [&](auto hd_tag) {
+        if (i16) width(hd_tag, std::true_type{});
+        else width(hd_tag, std::false_type{});
+    };
+    if (hd == 128) type(std::integral_constant<int, 128>{});
+    else type(std::integral_constant<int, 64>{});
 }

@@ -637,6 +637,45 @@ def test_paged_ragged_prefill_through_the_fused_projection_and_grouped_query_att
     assert worst <= LOGIT_TOL
 
 
+# block-scaled rows of both widths, half rows; prompts of one and of several key tiles
+@pytest.mark.parametrize("shape", [ModelShape(1, 256, 2, 2, 128, 688, 1000), ModelShape(1, 256, 4, 4, 64, 688, 1000),
+                                   ModelShape(1, 1024, 8, 2, 128, 688, 1000)])
+@pytest.mark.parametrize("T", [70, 200])
+def test_paged_prefill_attention_equals_contiguous_past_a_tile(shape, T):
+    """Ragged prompts whose lengths end inside, at and just past 32-row blocks and tiles, over caches that are full of NaN patterns: the
+    kernel for consecutive rows and the one for page lists give the same bits, and nothing of a row that does not exist."""
+    from paper_2406_14088_amd import Generator
+    page, lens = 16, [n for n in (1, 31, 32, 33, 63, 64, 65, 70, 128, 129, 191, 200) if n <= T]
+    B = len(lens)
+    W = make_weights(shape, 61, device="cpu")
+    Wg = {k: ([t.to(DEV) for t in v] if isinstance(v, list) else v.to(DEV)) for k, v in W.items()}
+    toks = make_prompts(Workload("t", 61, shape, B, T, 0)).to(DEV)
+    d_lens = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    n_pages = sum(-(-n // page) for n in lens)
+
+    def run(gen):
+        gen.kv_arena.fill_(255)
+        if gen.pool_pages():
+            gen.set_block_table(_shuffled_pages(lens, page, n_pages, 62), lens)
+        logits, nxt = gen.prefill_ragged(toks, d_lens)
+        torch.cuda.synchronize()
+        return logits, nxt
+
+    flat = Generator(shape, Wg, B, T)
+    want, nxt = run(flat)
+    paged = Generator(shape, Wg, B, T, page_size=page, n_pages=n_pages)
+    got, nxt2 = run(paged)
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32)) and torch.equal(nxt, nxt2)
+    Wn = orc.weights_to_numpy(W)
+    for b in (0, 3, B - 1):
+        om = orc.OracleModel(shape, Wn, 1, T)
+        ol, _ = om.prefill(toks[b: b + 1, : lens[b]].cpu().numpy())
+        assert np.abs(np64(want[b]) - ol[0]).max() <= LOGIT_TOL
+        om.close()
+    flat.close()
+    paged.close()
+
+
 def test_paged_cache_capacity_is_checked_on_the_host():
     """Nothing is launched that would store a row outside a sequence's pages: the calls fail with E_CAPACITY / E_STATE."""
     from paper_2406_14088_amd import Generator, RlGenError
