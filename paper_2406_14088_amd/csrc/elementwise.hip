@@ -350,8 +350,11 @@ __global__ __launch_bounds__(LP_THREADS) void logprob_gather_kernel(const float 
     }
     const float *row = logits + (size_t)blockIdx.x * ld;
     float m = -INFINITY, s = 0.f;
-    // 16 elements a trip with one rescale, as 16-byte loads where the rows allow it.  (One element a trip, with a branch and expf, streamed
-    // the logits at 2.5 TB/s: 8192 rows of 32000 382 us, 197 now, 2048 of 128256 344, 186 now, at no larger error against 64 bits.)
+    // 16 elements a trip with one rescale, as 16-byte loads (which need no more than the 4-byte alignment of a float), and what is left of a
+    // row as up to four such pieces and a single element: the sums of a row do not depend on where it lies.  (One element a trip, with a branch and expf,
+    // streamed the logits at 2.5 TB/s: 8192 rows of 32000 382 us, 197 now, 2048 of 128256 344, 186 now, at no larger error against 64 bits.
+    // 256 rows of 32001, where three rows of four begin off a 16-byte boundary: 28.5, now 8.1.)
+    typedef float piece_t __attribute__((ext_vector_type(4), aligned(4)));
     auto add = [&](auto &x) {
         constexpr int N = sizeof(x) / sizeof(float);
         float mn = m;
@@ -363,24 +366,37 @@ __global__ __launch_bounds__(LP_THREADS) void logprob_gather_kernel(const float 
         for (int k = 0; k < N; ++k) s += __builtin_amdgcn_exp2f((x[k] - at) * 1.44269504f);
         m = mn;
     };
-    int i0 = 0;
-    if ((reinterpret_cast<uintptr_t>(row) & 15) == 0) {
-        i0 = V / (16 * LP_THREADS) * (16 * LP_THREADS);
-        for (int i = 4 * t; i < i0; i += 16 * LP_THREADS) {
-            float x[16];
+    const int whole = V / (16 * LP_THREADS) * (16 * LP_THREADS);
+    for (int i = 4 * t; i < whole; i += 16 * LP_THREADS) {
+        float x[16];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const f32x4_t v = *reinterpret_cast<const f32x4_t *>(row + i + 4 * k * LP_THREADS);
+        for (int k = 0; k < 4; ++k) {
+            const piece_t v = *reinterpret_cast<const piece_t *>(row + i + 4 * k * LP_THREADS);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) x[4 * k + e] = v[e];
-            }
-            add(x);
+            for (int e = 0; e < 4; ++e) x[4 * k + e] = v[e];
         }
-    }
-    for (int i = i0 + t; i < V; i += LP_THREADS) {
-        float x[1] = {row[i]};
         add(x);
     }
+    const int pieces = V >> 2;  // all lanes that have one load it before the first is added
+    float x[4][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (whole / 4 + k * LP_THREADS >= pieces) break;
+        const int j = whole / 4 + t + k * LP_THREADS;
+        if (j < pieces) {
+            const piece_t v = *reinterpret_cast<const piece_t *>(row + 4 * j);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[k][e] = v[e];
+        }
+    }
+    const bool odd = t < (V & 3);
+    float last[1] = {odd ? row[4 * pieces + t] : 0.f};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (whole / 4 + k * LP_THREADS >= pieces) break;
+        if (whole / 4 + t + k * LP_THREADS < pieces) add(x[k]);
+    }
+    if (odd) add(last);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) lse_merge(m, s, __shfl_xor(m, o, 64), __shfl_xor(s, o, 64));
     if ((t & 63) == 0) { sm[t >> 6] = m; ss[t >> 6] = s; }

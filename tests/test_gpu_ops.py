@@ -537,6 +537,26 @@ def test_logprob_gather(ops, M, V, T, m_first):
             assert abs(on[gidx] - ref) <= 2e-5 * (1.0 + abs(ref)), (r, on[gidx], ref)
 
 
+@pytest.mark.parametrize("V", [1, 3, 97, 2049, 8191, 8193, 16389, 32001])
+@pytest.mark.parametrize("masked", [False, True])
+def test_logprob_gather_of_equal_rows(ops, V, masked):
+    """A row's log-probability does not depend on where the row lies (each of 48 rows four times; odd widths, so at every alignment of a
+    float), and logits of minus infinity have no share in it."""
+    rows = randn_f32((48, V), 95 + V, std=2.5)
+    if masked:
+        rows[:, : V // 2] = float("-inf")
+    logits = rows.repeat_interleave(4, 0).contiguous()
+    target = V - 1
+    tokens = torch.full((194,), target, dtype=torch.int32, device=DEV)
+    out = torch.empty((193,), dtype=torch.float32, device=DEV)
+    ops.logprob_gather(logits, tokens, 194, 0, out)
+    torch.cuda.synchronize()
+    ln, on = np64(rows), np64(out[:192]).reshape(48, 4)
+    ref = ln[:, target] - np.log(np.exp(ln).sum(1))
+    assert (np.abs(on - ref[:, None]) <= 2e-5 * (1.0 + np.abs(ref[:, None]))).all()
+    assert (on == on[:, :1]).all()
+
+
 def test_empty_inputs_enqueue_nothing(ops):
     """M = 0 / B = 0: every entry point returns success and leaves its outputs alone.  (Called through the C ABI directly:
     an empty torch tensor has a NULL pointer, which the entry points reject.)"""
