@@ -225,16 +225,21 @@ __global__ __launch_bounds__(AM_THREADS) void argmax_kernel(const float *__restr
     float bv = -INFINITY;
     int bi = 0x7fffffff;
     bool nan = false;
-    // eight loads in flight (one at a time the row is a chain of latencies: 16 rows of 32000 9.6 -> 8.1 us, of 128256 27.1 -> 20.7)
-    for (int i0 = t; i0 < V; i0 += 8 * AM_THREADS) {
-        float v[8];
+    auto take = [&](float v, int i) {
+        nan |= (v != v);
+        if (i < V && (v > bv || (v == bv && i < bi))) { bv = v; bi = i; }
+    };
+    // eight loads in flight (one at a time the row is a chain of latencies: 16 rows of 32000 9.6 -> 8.1 us, of 128256 27.1 -> 20.7), unless
+    // most of the eight would be past the row (one / eight at a time, us, 2048 rows of 1024 14.1 / 16.2, of 2500 16.1 / 16.6, of 4000 19.4 / 17.8)
+    if (V <= 3 * AM_THREADS) {
+        for (int i = t; i < V; i += AM_THREADS) take(row[i], i);
+    } else {
+        for (int i0 = t; i0 < V; i0 += 8 * AM_THREADS) {
+            float v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = i0 + u * AM_THREADS < V ? row[i0 + u * AM_THREADS] : -INFINITY;
+            for (int u = 0; u < 8; ++u) v[u] = i0 + u * AM_THREADS < V ? row[i0 + u * AM_THREADS] : -INFINITY;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int i = i0 + u * AM_THREADS;
-            nan |= (v[u] != v[u]);
-            if (i < V && (v[u] > bv || (v[u] == bv && i < bi))) { bv = v[u]; bi = i; }
+            for (int u = 0; u < 8; ++u) take(v[u], i0 + u * AM_THREADS);
         }
     }
 #pragma unroll

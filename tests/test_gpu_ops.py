@@ -514,6 +514,21 @@ def test_argmax(ops, V):
     assert int(nxt[1]) == min(17, 4000 % V) and int(nxt[2]) == 0 and int(nxt[3]) == V - 1 and int(nxt[4]) == -1
 
 
+@pytest.mark.parametrize("V", [1, 97, 3072, 3073, 8192, 8193])
+def test_argmax_at_the_edges_of_its_trips(ops, V):
+    """Largest value at both ends of the row, ties (lowest index), a row of minus infinity, a NaN in the last place."""
+    x = randn_f32((6, V), 93 + V)
+    x[1, -1] = 50.0
+    x[2, 0] = 50.0
+    x[3, V // 2:] = 50.0
+    x[4] = float("-inf")
+    x[5, -1] = float("nan")
+    nxt = torch.full((6,), 7, dtype=torch.int32, device=DEV)
+    ops.argmax(x, nxt)
+    torch.cuda.synchronize()
+    assert nxt.tolist() == [int(np64(x[0]).argmax()), V - 1, 0, V // 2, 0, -1]
+
+
 @pytest.mark.parametrize("M,V,T,m_first", [(7, 97, 4, 0), (64, 1000, 16, 32), (33, 32000, 11, 22), (5, 128256, 5, 0)])
 def test_logprob_gather(ops, M, V, T, m_first):
     """out[g] = log softmax(row)[next token]; rows that end a sequence get 0."""
