@@ -325,6 +325,7 @@ __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_pa
     // ---- epilogues.  Lane holds column (lane & 31) of its block; register e of tile mt is row
     //      32 mt + 8 (e / 4) + 4 (lane >> 5) + (e % 4).
     if (!swiglu) {
+        typedef float piece_t __attribute__((ext_vector_type(4), aligned(4)));
         float *ct = reinterpret_cast<float *>(smem);  // [BM][PK_CT_STRIDE]
         float *out = reinterpret_cast<float *>(p.out) + (size_t)split * p.split_stride;
         const bool accumulate = p.epilogue == EPI_F32_ACC;
@@ -452,9 +453,9 @@ __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_pa
                 if (m < Mloc && c4 < ncols && !(CAND && p.no_store)) {
                     f32x4_t v = *reinterpret_cast<const f32x4_t *>(ct + m * PK_CT_STRIDE + c4);
                     float *dst = out + (size_t)(m0 + m) * p.ldc + p.col_off[seg] + n_first + c4;
-                    if (c4 + 4 <= ncols && ((reinterpret_cast<uintptr_t>(dst) & 15) == 0)) {
-                        if (accumulate) v += *reinterpret_cast<const f32x4_t *>(dst);
-                        *reinterpret_cast<f32x4_t *>(dst) = v;
+                    if (c4 + 4 <= ncols) {  // a 16-byte access needs no more than the alignment of a float
+                        if (accumulate) v += *reinterpret_cast<const piece_t *>(dst);
+                        *reinterpret_cast<piece_t *>(dst) = v;
                     } else {
                         for (int e = 0; e < 4 && c4 + e < ncols; ++e) dst[e] = accumulate ? dst[e] + v[e] : v[e];
                     }

@@ -349,6 +349,26 @@ def test_gemm_packed_row_stride_and_accumulate(ops, M, nb, rpw):
     assert np.abs(np64(out) - ref).max() <= 1e-4
 
 
+@pytest.mark.parametrize("N,shift", [(301, 0), (257, 1), (130, 3), (3, 0)])
+@pytest.mark.parametrize("nb,rpw", [(1, 64), (2, 128)])
+@pytest.mark.parametrize("epilogue", [0, 2])
+def test_gemm_packed_output_rows_at_any_float(ops, N, shift, nb, rpw, epilogue):
+    """Output rows of odd length, beginning off a 16-byte boundary: whole pieces and tails, and nothing beside them."""
+    M, K = 150, 72
+    A, W = randn_f16((M, K), 320), randn_bf16((N, K), 321, std=0.05)
+    P = torch.empty((ops.packed_weight_bytes(N, K) // 2,), dtype=torch.int16, device=DEV)
+    ops.pack_weights(W, P)
+    flat = torch.full((shift + M * (N + 2) + 8,), 3.0, dtype=torch.float32, device=DEV)
+    ops.gemm_packed(A, [P], [N], K, flat[shift:], N + 2, M=M, split_stride=0, splits=1, epilogue=epilogue, nb=nb, rows_per_wg=rpw, depth=2)
+    torch.cuda.synchronize()
+    got = np64(flat)
+    inside = got[shift: shift + M * (N + 2)].reshape(M, N + 2)
+    a, w = np64(A), np64(W)
+    ref = a @ w.T + (3.0 if epilogue == 2 else 0.0)
+    assert (np.abs(inside[:, :N] - ref) <= 2.0 ** -24 * (K + 1) * (np.abs(a) @ np.abs(w).T + 3.0)).all()
+    assert (inside[:, N:] == 3.0).all() and (got[:shift] == 3.0).all() and (got[shift + M * (N + 2):] == 3.0).all()
+
+
 @pytest.mark.parametrize("M,K,F,rpw", [(4, 256, 688, 0), (128, 512, 1000, 32), (256, 256, 72, 64), (130, 1000, 4128, 128)])
 def test_gemm_packed_swiglu(ops, M, K, F, rpw):
     step(f"packed swiglu M={M} K={K} F={F} rows_per_wg={rpw}")
