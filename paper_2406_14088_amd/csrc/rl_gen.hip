@@ -311,7 +311,7 @@ int project(rl_gen *h, int cls, const f16_t *A, const f16_t *A_lo, int64_t lda, 
     }
     if (acc_out) {
         if (a.A_lo && P0 && !W1 && !W2) {
-            // two activation terms from the fragment-order copy: 128-row workgroups of the decode kernel, two per compute
+            // two activation terms from the fragment-order copy: workgroups of the decode kernel, two per compute
             // unit (they hide each other's barriers and epilogues), run ahead of the tile kernel (16384 rows, 7B shape: O 0.88
             // against 0.95 ms, down 2.27 against 2.59); with one term the tile kernel is ahead
             PackedGemmArgs q;
@@ -333,10 +333,9 @@ int project(rl_gen *h, int cls, const f16_t *A, const f16_t *A_lo, int64_t lda, 
     return 1;
 }
 
-// QKV projection of a prefill from the fragment-order copies: 128-row workgroups of the packed kernel, whose epilogue rotates q
-// and k and stores q and the cache rows.  16384 rows of the 7B shape: two terms and block-scaled rows 2520 us (tile kernel
+// QKV projection of a prefill from the fragment-order copies: tiles of the packed kernel (gemm_packed_tile_plan), whose epilogue
+// rotates q and k and stores q and the cache rows.  16384 rows of the 7B shape: two terms and block-scaled rows 2520 us (tile kernel
 // from copies 3290, from row-major weights 3430), one term and half rows 1440 (2134 from copies).
-// Short prompts and narrow models run in smaller tiles (gemm_packed_tile_plan).
 void rope_projection_from_copies(const f16_t *A, const f16_t *A_lo, int64_t lda, int M, int K, const f16_t *Pq, const f16_t *Pk,
                                  const f16_t *Pv, const RopeEpilogue &rp, hipStream_t st) {
     PackedGemmArgs q;
@@ -1130,16 +1129,19 @@ int rl_gen_logprobs(rl_gen_t *h, const int32_t *tokens, int32_t B, int32_t T, fl
                 Scope sc(h, RL_GEN_K_GEMM_LM_HEAD, st);
                 if (lo) a.A_lo = a.A + (size_t)M * s.hidden;
                 if (h->packed) {
-                    // From the copy, in the workgroups of the other prefill projections (few rows: of the decode step).  A call of one
-                    // layer, tile kernel from row-major weights -> here, us: hidden 4096, vocabulary 32000, 12288 rows 10935 -> 10081,
-                    // 200 rows 441 -> 376, 40 rows 230 -> 215; vocabulary 128256, 4096 rows 12696 -> 9579; two terms, hidden 5120, 7992
-                    // rows 14281 -> 12767.
+                    // From the copy, in the tiles of the other prefill projections (few rows: of the decode step).  A call of one layer,
+                    // tile kernel from row-major weights -> here, us: hidden 4096, vocabulary 32000, 12288 rows 10935 -> 10081, 200 rows
+                    // 441 -> 376, 40 rows 230 -> 215; vocabulary 128256, 4096 rows 12696 -> 9579; two terms, hidden 5120, 7992 rows
+                    // 14281 -> 12767.  The projection alone, hidden 256, vocabulary 1024: 257 rows 10.1 -> 7.5 (13.3 in tiles of
+                    // 128 x 256, which are 12 workgroups there); hidden 1024, vocabulary 50257 (rows at any float): 4000 rows 81 -> 44.
                     PackedGemmArgs q;
                     q.A = a.A; q.A_lo = a.A_lo; q.lda = a.lda; q.M = mm; q.K = a.K;
                     q.P[0] = h->p_lm_head; q.P[1] = nullptr; q.P[2] = nullptr;
                     q.rows[0] = s.vocab; q.rows[1] = 0; q.rows[2] = 0;
                     q.out = a.out; q.ldc = s.vocab; q.split_stride = 0; q.splits = 1; q.epilogue = EPI_F32;
-                    q.nb = mm > kSkinnyMaxM ? 2 : 1; q.rows_per_wg = 128; q.depth = 2;
+                    if (mm > kSkinnyMaxM) gemm_packed_tile_plan(mm, q.rows, &q.nb, &q.rows_per_wg);
+                    else { q.nb = 1; q.rows_per_wg = 128; }
+                    q.depth = 2;
                     launch_gemm_packed(q, st);
                 } else if (mm <= kSkinnyMaxM && !lo) launch_gemm_skinny(a, st);
                 else launch_gemm_tiled(a, st);
