@@ -105,18 +105,19 @@ __device__ __forceinline__ uint32_t pack_f16x2_lo(float x0, float x1, uint32_t h
 }
 
 // g / (1 + e^-g) * u.  e^-g = 2^t with the rounding error of t = -g log2(e) carried to first order; the quotient by the hardware's
-// reciprocal and one correction with its remainder: the accuracy of expf and an IEEE division at half their instructions.  From |g| = 87
-// on the quotient is g itself or, below 1.5e-36 in magnitude, -0 (NaN for a gate of minus infinity, as -inf / inf is); the remainder
-// of an infinite quotient would be NaN.  A NaN in g or u stays one.
+// reciprocal and one correction with its remainder: the accuracy of expf and an IEEE division at half their instructions.  Below
+// g = -87 the factor of g stays at e^-87 (1.6e-38: nothing in a half for any gate and up sum that halves can produce), above 100 at 1.
+// An infinite gate takes the remainder from the largest finite quotient, so that it gives inf (and -inf a NaN, as -inf / inf is).  A NaN
+// in g or u stays one.  (Selecting the result for large |g| instead took 2 % of a gate/up projection of 256 rows, 72.5 -> 74.3 us.)
 __device__ __forceinline__ float silu_mul(float g, float u) {
-    const float t = g * -1.44269504f;
-    const float r = __builtin_fmaf(g, -1.92596299e-8f, __builtin_fmaf(g, -1.44269504f, -t));  // what t lacks of -g log2(e)
+    const float x = __builtin_amdgcn_fmed3f(g, -87.f, 100.f);
+    const float t = x * -1.44269504f;
+    const float r = __builtin_fmaf(x, -1.92596299e-8f, __builtin_fmaf(x, -1.44269504f, -t));  // what t lacks of -x log2(e)
     const float e = __builtin_amdgcn_exp2f(t);
     const float d = 1.0f + __builtin_fmaf(e, r * 0.693147181f, e);
     const float q = __builtin_amdgcn_rcpf(d);
-    const float s = g * q;
-    const float y = __builtin_fmaf(__builtin_fmaf(-d, s, g), q, s);
-    return (fabsf(g) < 87.f ? y : (g > 0.f ? g : g * 0.f)) * u;
+    const float s = fminf(g * q, 3.40282347e38f);
+    return __builtin_fmaf(__builtin_fmaf(-d, s, g), q, s) * u;
 }
 
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
