@@ -179,12 +179,23 @@ __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_pa
     const int c1 = (int)(((int64_t)(split + 1) * p.chunks) / p.splits);
     const int ks_end = c1 * 4 < p.ksteps ? c1 * 4 : p.ksteps;
 
-    __amdgpu_buffer_rsrc_t wr[NB];  // ends with the K range: loads past it return zeros and touch no memory
+    // A fragment that does not exist (past the K range, or a block past the matrix) reads as zeros and touches no memory.  Prefill tiles
+    // of 128 rows: the descriptor ends there, so an offset is the lane's plus a scalar -- 2 % ahead of the other form (16384 rows, 7B shape,
+    // two terms: QKV 2398 against 2456 us, O 822 / 838, down 2106 / 2140; 70B shape one 3902 / 3986, 3128 / 3188, 11097 / 11399).  Few rows, which
+    // live on the weight stream: a comparison per fragment and an offset in a register -- 2-5 % ahead (two-term gate/up 13B shape, 24
+    // rows 70.5 against 73.2 us, 34B shape 122.7 / 128.5, 64 rows 137.1 / 141.0; 70B shape, 128 rows 255 / 262, down 123 / 127; O 64 rows 34.4 / 36.3).
+    constexpr bool SCALAR = MT == 4 && !SW;
+    __amdgpu_buffer_rsrc_t wr[NB];
+    uint32_t w_off[NB];
+    bool w_ok[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         int nb = swiglu ? ltile * 4 + w : (ltile * NB + j) * 4 + w;
         const f16_t *P = swiglu ? (j == 0 ? p.P[0] : p.P[1]) : (seg == 0 ? p.P[0] : (seg == 1 ? p.P[1] : p.P[2]));
-        wr[j] = pk_rsrc(P + (nb < nblocks ? (size_t)nb * p.ksteps * 512 : 0), nb < nblocks ? (uint32_t)ks_end * 1024u : 0u);
+        w_ok[j] = nb < nblocks;
+        w_off[j] = ((uint32_t)nb * (uint32_t)p.ksteps * 64u + (uint32_t)lane) * 16u;
+        wr[j] = SCALAR ? pk_rsrc(P + (w_ok[j] ? (size_t)nb * p.ksteps * 512 : 0), w_ok[j] ? (uint32_t)ks_end * 1024u : 0u)
+                       : pk_rsrc(P, (uint32_t)((size_t)nblocks * p.ksteps * 1024));
     }
 
     // ---- activation copy global -> LDS.  Instruction i of wavefront w fills the 1 KB block of rows
@@ -230,7 +241,9 @@ __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_pa
         // With one row block every weight byte is used once: a streaming (non-temporal) load, which this part's memory
         // system moves faster than a cached one (7.05 against 6.2 TB/s on plain streaming).  With more row blocks the
         // other blocks of the tile are meant to find the fragment in L2.
-        ring[slot] = __builtin_amdgcn_raw_buffer_load_b128(wr[j], (c * 4 + s) * 1024 + lane * 16, 0, SW ? 3 : 0);
+        const int ks = c * 4 + s;
+        const uint32_t off = SCALAR ? (uint32_t)(ks * 1024 + lane * 16) : (ks < ks_end && w_ok[j] ? w_off[j] + (uint32_t)ks * 1024u : PK_OOB);
+        ring[slot] = __builtin_amdgcn_raw_buffer_load_b128(wr[j], (int)off, 0, SW ? 3 : 0);
     };
 
     f32x16_t acc[NB][MT];
