@@ -839,10 +839,11 @@ void launch_gemm_packed_swiglu_halves(const PackedGemmArgs &a, hipStream_t st) {
     else launch_halves<4, false>(p, st);  // several row blocks: the single-operation entry point only
 }
 
-// Decomposition of a projection with fp32 partial outputs.  Measured inside whole decode steps of the 7B shape,
-// one 128-row workgroup per column tile and split-K up to about one workgroup per compute unit was as fast as
-// any mix of 64-row workgroups, two column blocks per wavefront and deeper splits (all within 3 %).
-void gemm_packed_plan(int N, int K, int M, int *nb, int *rows_per_wg, int *splits) {
+// Decomposition of a projection with fp32 partial outputs: one workgroup of up to 128 rows per column tile of 128, and K split up to about
+// one workgroup per compute unit.  Inside whole decode steps of the 7B shape 64-row workgroups and deeper splits of tiles of 128
+// columns were within 3 % of that.
+// batch: the most rows that a step of the caller can have, M or more.
+void gemm_packed_plan(int N, int K, int M, int batch, int *nb, int *rows_per_wg, int *splits) {
     int chunks = ceil_div(K, PK_BK);
     *nb = 1;
     *rows_per_wg = M <= 32 ? 32 : (M <= 64 ? 64 : 128);
@@ -853,17 +854,18 @@ void gemm_packed_plan(int N, int K, int M, int *nb, int *rows_per_wg, int *split
     if (s > 16) s = 16;
     if (s < 1) s = 1;
     *splits = s;
-    // Workgroups twice as wide over half of K.  A compute unit's loads return in order, activations from L2 behind weights from HBM, so
-    // what counts is the bytes it loads in all, and twice the columns halve the activations; the price is twice the partials.
+    // Twice the splits, in workgroups twice as wide.  A compute unit's loads return in order, activations from L2 behind weights from
+    // HBM, so what counts is the bytes it loads in all, and twice the columns halve the activations; the price is twice the partials.
     // Worth it where two row blocks leave no K split (two terms, 256 rows, us: 15360 x 5120 94.6 -> 82.7, 12288 x 4096 70.2 -> 56.2;
     // 160 rows 93.1 -> 75.8, 60.7 -> 55.3) and where a split still is 64 chunks or more (28672 -> 8192, 48 / 64 / 128 rows 88.6 -> 80.1,
     // 94.4 -> 84.5, 136 -> 126; 22016 -> 8192, 64 rows 75 -> 69); not for shorter ones (8192 -> 8192 of 64 rows, 32 chunks, 30.8 against
-    // 36.9; 14336 -> 4096 29.9 / 35.5).  Up to 32 rows either is level (28672 -> 8192 73 / 73, 78 / 77) and takes the same split: the
-    // sums of a batch of up to 128 rows keep their order when it shrinks.
-    if ((M > 128 && s == 1) || chunks / s >= 64) {
+    // 36.9; 14336 -> 4096 29.9 / 35.5; nothing between 32 and 64 chunks was measured).  Up to 32 rows the partials cost more than the
+    // activations (28672 -> 8192, 1 / 16 rows 70.6 / 71.5 -> 72.3 / 74.4, and the norm that adds them 7.1 -> 7.7): they keep the plain plan unless
+    // they are what is left of a larger batch, whose sums keep their order; those run in tiles of 128 columns (73.2 at 16 rows).
+    if ((M > 128 && s == 1) || (chunks / s >= 64 && batch > 32)) {
         const int wide = ceil_div(N, 256) * ceil_div(M, *rows_per_wg);
         if (2 * s <= 16 && wide * 2 * s <= 256 && chunks >= 16 * s) {
-            *nb = 2;
+            *nb = M <= 32 ? 1 : 2;
             *splits = 2 * s;
         }
     }

@@ -145,7 +145,7 @@ void launch_gemm_packed(const PackedGemmArgs &a, hipStream_t st);
 // formed in the order of launch_gemm_skinny's and equal them bit for bit.  a.P[0] = gate, a.P[1] = up, a.rows[0] = F.
 bool gemm_packed_swiglu_halves_supported(int F, int K);
 void launch_gemm_packed_swiglu_halves(const PackedGemmArgs &a, hipStream_t st);
-void gemm_packed_plan(int N, int K, int M, int *nb, int *rows_per_wg, int *splits);
+void gemm_packed_plan(int N, int K, int M, int batch, int *nb, int *rows_per_wg, int *splits);
 void gemm_packed_tile_plan(int M, const int rows[3], int *nb, int *rows_per_wg);  // prefill: no K split
 
 // ---- attention_decode.hip ------------------------------------------------------------------------

@@ -278,7 +278,8 @@ int project_packed(rl_gen *h, int cls, const f16_t *A, const f16_t *A_lo, int64_
     a.rows[0] = r0; a.rows[1] = r1; a.rows[2] = r2;
     int N = r0 + r1 + r2;
     int splits;
-    gemm_packed_plan(N, K, M, &a.nb, &a.rows_per_wg, &splits);
+    // by the capacity, not by the batch at hand: sums keep their order when a batch shrinks
+    gemm_packed_plan(N, K, M, M > h->s.max_batch ? M : h->s.max_batch, &a.nb, &a.rows_per_wg, &splits);
     a.depth = 2;
     if (splits > kMaxSplits) splits = kMaxSplits;
     a.out = h->part(); a.ldc = N; a.split_stride = (size_t)M * N; a.splits = splits; a.epilogue = EPI_F32;
@@ -1508,7 +1509,7 @@ int rl_op_gemm_packed(const uint16_t *A, const uint16_t *A_lo, int64_t lda, cons
     a.rows[0] = rows0; a.rows[1] = rows1; a.rows[2] = rows2;
     a.out = out; a.ldc = ldc; a.split_stride = split_stride; a.splits = splits; a.epilogue = epilogue; a.out_lo = out_lo;
     int pnb, prows, psplits;
-    gemm_packed_plan(rows0 + rows1 + rows2, K, M, &pnb, &prows, &psplits);
+    gemm_packed_plan(rows0 + rows1 + rows2, K, M, M, &pnb, &prows, &psplits);
     a.nb = nb ? nb : (splits < psplits ? 1 : pnb);  // the wide workgroups of the plan come with its K split
     a.rows_per_wg = rows_per_wg;
     a.depth = depth;

@@ -968,6 +968,38 @@ def test_batch_compaction_after_the_end_token(cache, graph):
     assert worst <= LOGIT_TOL
 
 
+def test_fewer_rows_keep_the_bits_of_a_down_projection_in_doubled_splits():
+    """28672 -> 8192: a generator of more than 32 sequences runs it in 8 splits at every batch up to 128 rows, in tiles of 256 or (up to 32
+    rows) 128 columns, so 24 of 40 sequences give the bits that they give among the 40; one of up to 32 in 4: the same to rounding."""
+    from paper_2406_14088_amd import Generator
+    shape = ModelShape(1, 8192, 64, 8, 128, 28672, 1000)
+    g = torch.Generator(device=DEV).manual_seed(63)
+    mat = lambda n, k: (torch.randn((n, k), generator=g, device=DEV) * 0.02).to(torch.bfloat16)
+    one = torch.ones(8192, dtype=torch.bfloat16, device=DEV)
+    W = {"tok_emb": mat(1000, 8192), "lm_head": mat(1000, 8192), "final_norm": one, "attn_norm": [one], "ffn_norm": [one], "wq": [mat(8192, 8192)],
+         "wk": [mat(1024, 8192)], "wv": [mat(1024, 8192)], "wo": [mat(8192, 8192)], "w_gate": [mat(28672, 8192)], "w_up": [mat(28672, 8192)],
+         "w_down": [mat(8192, 28672)]}
+    prompts = torch.randint(0, 1000, (40, 16), generator=g, device=DEV, dtype=torch.int32)
+
+    def run(gen, n):
+        gen.reset()
+        gen.prefill(prompts[:n].contiguous())
+        logits, _ = gen.decode_step(prompts[:n, 3].contiguous())
+        logits, _ = gen.decode_step(prompts[:n, 5].contiguous())
+        torch.cuda.synchronize()
+        return logits.clone()
+
+    gen = Generator(shape, W, 40, 20)
+    full, part = run(gen, 40), run(gen, 24)
+    gen.close()
+    small = Generator(shape, W, 24, 20)
+    alone = run(small, 24)
+    small.close()
+    assert torch.equal(full[:24].view(torch.int32), part.view(torch.int32))
+    rel = float((alone - part).double().norm() / part.double().norm())
+    assert rel < 1e-4, rel     # level 3: every activation in two half terms
+
+
 @pytest.mark.parametrize("kv_heads", [32, 8])
 def test_compaction_keeps_the_bits_where_decode_attention_changes_its_split(kv_heads):
     """70 sequences are one wavefront per sequence and head (or per 4 query heads), fewer than 64 alone would be four: what a
