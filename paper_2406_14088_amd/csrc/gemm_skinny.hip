@@ -54,8 +54,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint3
 
 // MT: 32-row tiles of activations per workgroup (1, 2 or 4; grid.z walks taller batches): the matrix instructions, the staging and the
 // epilogue of 128 rows cost a batch of 16 as much as one of 128.
-// SW: one row block, every weight byte is used once and is loaded non-temporally (streams faster than a cached load).
-template <int MT, bool SW>
+// With one row block every weight byte is used once and is loaded non-temporally (streams faster than a cached load).  Workgroups of 128
+// rows, which may have several row blocks, test that per load: the branch ends the compiler's scheduling region and makes its waits stricter, and with two chunks in flight
+// that is the faster order (11008 x 4096, 128 / 256 rows 31.6 / 46.0 us so, 32.5 / 48.1 as a template parameter; 12288 x 4096 32.8 / 46.6 and
+// 34.3 / 49.3; 32000 x 4096 59.1 / 118.5 and 61.4 / 124.8).
+template <int MT>
 __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int BM = 32 * MT, R = MT <= 2 ? 4 : 2;  // R: chunks in flight
@@ -118,6 +121,7 @@ __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams
     }
     u32x4_t xr[R][MT];  // activation pieces in flight: xr[i % R] belongs to chunk c0 + i
     u32x4_t wq[4 * R];  // raw bf16 weight pieces in flight: slots (i % R) * 4 .. + 3 belong to chunk c0 + i
+    const bool stream_w = gridDim.z == 1;
     f32x16_t acc[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -140,7 +144,8 @@ __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams
     };
     auto load_w1 = [&](int c, int slot, int i) {  // piece i of chunk c -> ring slot
         uint32_t cb = (uint32_t)c * (SK_BK * 2);
-        wq[slot] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)(c < c1 ? w_off[i] + cb : SK_OOB), 0, SW ? 3 : 0);
+        if (MT < 4 || stream_w) wq[slot] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)(c < c1 ? w_off[i] + cb : SK_OOB), 0, 3);
+        else wq[slot] = __builtin_amdgcn_raw_buffer_load_b128(wr, (int)(c < c1 ? w_off[i] + cb : SK_OOB), 0, 0);
     };
     auto stage_w1 = [&](int slot, int buf, int i) {  // ring slot -> half -> LDS strip `buf`
         *reinterpret_cast<u32x4_t *>(wl + buf * 4096 + i * 1024 + wst[i]) = bf16x8_to_f16x8(wq[slot]);
@@ -189,10 +194,16 @@ __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams
             load_x(c0 + r, r);
 #pragma unroll
             for (int i = 0; i < 4; ++i) load_w1(c0 + r, r * 4 + i, i);
+            if (r == 0 && MT == 4) {  // behind a load with a branch the compiler waits for all loads: before there are more of them
+#pragma unroll
+                for (int i = 0; i < MT; ++i) store_x1(0, 0, i);
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (MT < 4) {
 #pragma unroll
-        for (int i = 0; i < MT; ++i) store_x1(0, 0, i);
+            for (int i = 0; i < MT; ++i) store_x1(0, 0, i);
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             stage_w1(i, 0, i);
@@ -313,12 +324,12 @@ int gemm_skinny_default_splits(int M, int N, int K) {
     return s;
 }
 
-template <int MT, bool SW>
+template <int MT>
 static void launch_skinny(const SkinnyParams &p, dim3 grid, hipStream_t st) {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_skinny_kernel<MT, SW>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_skinny_kernel<MT>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     (void)attr;
-    gemm_skinny_kernel<MT, SW><<<grid, SK_THREADS, SK_X_BYTES(MT) + SK_W_BYTES, st>>>(p);
+    gemm_skinny_kernel<MT><<<grid, SK_THREADS, SK_X_BYTES(MT) + SK_W_BYTES, st>>>(p);
 }
 
 void launch_gemm_skinny(const GemmArgs &a, hipStream_t st) {
@@ -350,8 +361,7 @@ void launch_gemm_skinny(const GemmArgs &a, hipStream_t st) {
     p.tile_begin[3] = tiles;
     if (tiles <= 0) return;
     const dim3 grid(tiles, p.splits, ceil_div(a.M, a.M <= 32 ? 32 : (a.M <= 64 ? 64 : 128)));
-    if (a.M <= 32) launch_skinny<1, true>(p, grid, st);
-    else if (a.M <= 64) launch_skinny<2, true>(p, grid, st);
-    else if (a.M <= 128) launch_skinny<4, true>(p, grid, st);
-    else launch_skinny<4, false>(p, grid, st);
+    if (a.M <= 32) launch_skinny<1>(p, grid, st);
+    else if (a.M <= 64) launch_skinny<2>(p, grid, st);
+    else launch_skinny<4>(p, grid, st);
 }
