@@ -55,13 +55,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint3
 // MT: 32-row tiles of activations per workgroup (1, 2 or 4; grid.z walks taller batches): the matrix instructions, the staging and the
 // epilogue of 128 rows cost a batch of 16 as much as one of 128.
 // With one row block every weight byte is used once and is loaded non-temporally (streams faster than a cached load).  Workgroups of 128
-// rows, which may have several row blocks, test that per load: the branch ends the compiler's scheduling region and makes its waits stricter, and with two chunks in flight
-// that is the faster order (11008 x 4096, 128 / 256 rows 31.6 / 46.0 us so, 32.5 / 48.1 as a template parameter; 12288 x 4096 32.8 / 46.6 and
-// 34.3 / 49.3; 32000 x 4096 59.1 / 118.5 and 61.4 / 124.8).
-template <int MT>
+// rows, which may have several row blocks, test that per load: the branch ends the compiler's scheduling region and makes its waits
+// stricter, and with two chunks in flight that is the faster order (128 / 256 rows, us, so and as a template parameter: 11008 x 4096 30.7 / 46.0
+// and 31.9 / 48.1, 12288 x 4096 32.5 / 46.6 and 33.4 / 48.3, 32000 x 4096 59.0 / 118.0 and 60.1 / 120.6).
+// R: chunks in flight; the loop makes trips in multiples of it.
+template <int MT, int R>
 __global__ __launch_bounds__(SK_THREADS, 2) void gemm_skinny_kernel(SkinnyParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int BM = 32 * MT, R = MT <= 2 ? 4 : 2;  // R: chunks in flight
+    constexpr int BM = 32 * MT;
     f16_t *xs = reinterpret_cast<f16_t *>(smem);  // [2][BM][SK_LDS_STRIDE]
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);  // wavefront id as a scalar: descriptors stay in SGPRs
@@ -324,12 +325,12 @@ int gemm_skinny_default_splits(int M, int N, int K) {
     return s;
 }
 
-template <int MT>
+template <int MT, int R>
 static void launch_skinny(const SkinnyParams &p, dim3 grid, hipStream_t st) {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_skinny_kernel<MT>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_skinny_kernel<MT, R>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     (void)attr;
-    gemm_skinny_kernel<MT><<<grid, SK_THREADS, SK_X_BYTES(MT) + SK_W_BYTES, st>>>(p);
+    gemm_skinny_kernel<MT, R><<<grid, SK_THREADS, SK_X_BYTES(MT) + SK_W_BYTES, st>>>(p);
 }
 
 void launch_gemm_skinny(const GemmArgs &a, hipStream_t st) {
@@ -361,7 +362,9 @@ void launch_gemm_skinny(const GemmArgs &a, hipStream_t st) {
     p.tile_begin[3] = tiles;
     if (tiles <= 0) return;
     const dim3 grid(tiles, p.splits, ceil_div(a.M, a.M <= 32 ? 32 : (a.M <= 64 ? 64 : 128)));
-    if (a.M <= 32) launch_skinny<1>(p, grid, st);
-    else if (a.M <= 64) launch_skinny<2>(p, grid, st);
-    else launch_skinny<4>(p, grid, st);
+    // K of one or two chunks per split: two trips instead of four (688 x 256, 64 rows 7.5 us, with four trips 9.2, in workgroups of 128 rows 8.8)
+    const bool brief = ceil_div(p.chunks, p.splits) <= 2;
+    if (a.M <= 32) launch_skinny<1, 4>(p, grid, st);
+    else if (a.M <= 64) brief ? launch_skinny<2, 2>(p, grid, st) : launch_skinny<2, 4>(p, grid, st);
+    else launch_skinny<4, 2>(p, grid, st);
 }

@@ -1159,7 +1159,7 @@ def test_prefill_attention_value_scales_zero_negative_and_far_apart(ops, hd, T):
 
 
 @pytest.mark.parametrize("M", [1, 32, 33, 64, 65, 129])
-@pytest.mark.parametrize("K,splits", [(128, 1), (520, 1), (1160, 2), (1664, 3), (640, 1)])
+@pytest.mark.parametrize("K,splits", [(128, 1), (520, 1), (1160, 2), (1664, 3), (640, 1), (256, 1), (384, 1), (512, 2)])
 def test_gemm_skinny_row_tiles(ops, M, K, splits):
     """Edges of the row tiles (32, 64, 128), chunk counts around the depth of the ring (1, 5, 10, 13 in splits, 5)."""
     N = 200
