@@ -1312,13 +1312,25 @@ def test_qkv_projection_with_rotary_epilogue_block_scaled_equals_the_two_kernels
         assert (np.abs(deq - want) <= 0.51 * np64(sc)[:, None] + 2e-4).all(), name
 
 
-@pytest.mark.parametrize("Hq,Hkv,T,nseq,two,bs,page", [(2, 2, 40, 4, True, True, 0), (3, 1, 7, 37, False, False, 0), (8, 2, 33, 34, True, False, 16),
-                                                       (1, 1, 300, 1, True, True, 64), (5, 3, 65, 2, True, True, 0), (9, 3, 119, 15, True, True, 0),
-                                                       (9, 3, 113, 17, False, False, 16), (8, 8, 131, 10, True, False, 0)])
-def test_gemm_packed_rope_equals_projection_then_rope_append(ops, Hq, Hkv, T, nseq, two, bs, page):
-    """The fused epilogue stores the bits that the packed projection (fp32) followed by rope_append stores: prompts shorter and
-    longer than a row block, odd head counts (a last column tile of one head), paged pools; rows beyond a sequence's own
-    length stay out of the cache.  126 tiles of 128 rows x 2 heads and fewer run as tiles of 64 rows x 1 head; 132 and 144 as they are."""
+def _prefill_tile(M, heads):
+    """rows x heads (of 128 columns) of the tiles of a QKV projection: the smallest that one workgroup per compute unit covers"""
+    blocks = -(-M // 64)
+    two = sum(-(-h // 2) for h in heads)
+    if sum(heads) * blocks <= 256:
+        return 64, 1
+    return (64, 2) if two * blocks <= 256 else (128, 2)
+
+
+@pytest.mark.parametrize("Hq,Hkv,T,nseq,two,bs,page,tile", [
+    (2, 2, 40, 4, True, True, 0, (64, 1)), (3, 1, 7, 37, False, False, 0, (64, 1)), (8, 2, 33, 34, True, False, 16, (64, 1)),
+    (1, 1, 300, 1, True, True, 64, (64, 1)), (5, 3, 65, 2, True, True, 0, (64, 1)), (9, 3, 119, 15, True, True, 0, (64, 2)),
+    (8, 8, 131, 10, True, False, 0, (64, 2)), (9, 3, 113, 15, False, False, 16, (64, 2)), (9, 3, 113, 17, False, False, 16, (128, 2)),
+    (8, 8, 131, 11, True, True, 0, (128, 2)), (8, 8, 131, 11, True, False, 0, (128, 2)), (9, 3, 119, 17, True, True, 16, (128, 2))])
+def test_gemm_packed_rope_equals_projection_then_rope_append(ops, Hq, Hkv, T, nseq, two, bs, page, tile):
+    """The fused epilogue stores the bits that the packed projection (fp32) followed by rope_append stores, in each of the three tiles:
+    prompts shorter and longer than a row block, odd head counts (a last column tile of one head), paged pools; rows beyond a
+    sequence's own length stay out of the cache."""
+    assert _prefill_tile(nseq * T, (Hq, Hkv, Hkv)) == tile
     step(f"packed rope heads={Hq}/{Hkv} T={T} nseq={nseq} two={two} bs={bs} page={page}")
     hd, K, b0, S = 128, 200, 1, T + 9
     M, n_all = nseq * T, (Hq + 2 * Hkv) * hd
