@@ -15,8 +15,8 @@
 // Softmax and accumulation are fp32; probabilities are rounded to half for the matrix cores (two terms over block-scaled rows).
 //
 // What bounds it: long prompts the matrix cores together with the vector work of the softmax (719-886 TFLOP/s executed at 2048 and
-// 4096 positions); short ones the chain of latencies of a wavefront's tiles: of 6500 cycles per 32 keys with one wavefront per SIMD, 2000
-// are the two products, 1700 the softmax, 1300 the conversion to LDS.  What keeps the rest of that chain short:
+// 4096 positions); short ones the chain of latencies of a wavefront's tiles: of 5800 cycles per 32 keys with one wavefront per SIMD, 2200
+// are the two products, 1750 the softmax, 1300 the conversion to LDS.  What keeps the rest of that chain short:
 //   * consecutive rows are read through descriptors (one address register per operand and no comparison; rows of page lists, and
 //     sequences beyond 32-bit offsets, by a general path: template parameter LINEAR);
 //   * K and V fragments are read one product ahead; the queries are requested behind the first tile and arrive while it is staged;
@@ -76,9 +76,9 @@ __device__ __forceinline__ float pa_max32(float v) {
 __device__ __forceinline__ uint32_t pa_exponent(float v) { return __float_as_uint(v) & 0x7f800000u; }
 
 // LDS of one buffer: K [terms][KT][HD + 8] and V^T [terms][HD][KT + 8] halves, then (block-scaled rows) the score factors and
-// the normalised value scales [KT] and of every 32 rows the value reference and the mask of rows without a finite scale.  Both row strides are 4 banks modulo 16, which keeps
-// the 16-byte fragment reads free of conflicts; the 16-byte pieces of a V^T row are permuted by the row's 16-row group so that the
-// transposing 8-byte stores of a wavefront spread over all banks.
+// the normalised value scales [KT] and of every 32 rows the value reference and the mask of rows without a finite scale.  Both row
+// strides are 4 banks modulo 16, which keeps the 16-byte fragment reads free of conflicts; the 16-byte pieces of a V^T row are permuted
+// by the row's 16-row group so that the transposing 8-byte stores of a wavefront spread over all banks.
 template <int HD, bool I16, int NW>
 struct PaTile {
     static constexpr int KT = 8 * NW, NT = I16 ? 2 : 1;
@@ -92,7 +92,7 @@ struct PaTile {
 // I16: the cache rows are 16-bit block-scaled fixed point (KvMap::kscale / vscale).  A row element has more
 // significant bits than a half holds, so it enters the matrix cores as a two-term half sum hi + lo, and so do the
 // probabilities and -- when q_lo is given -- the queries: each of the two products of a tile becomes three matrix
-// instructions (hi x hi, lo x hi, hi x lo; lo x lo is below fp32 resolution) and no operand carries a single half rounding.
+// instructions (hi x hi, lo x hi, hi x lo; lo x lo is at most 2^-24 of a product) and no operand carries a single half rounding.
 // A probability is multiplied with its row's value scale before it is split; so that the product stays in the normal range of a
 // half, scales are taken relative to a power of two, the one at or below the largest scale up to the 32 rows at hand (the reference,
 // part of the online rescale).  The grid of the low term is 2^-25 of a probability for rows of 2^-14 of the reference and larger, the

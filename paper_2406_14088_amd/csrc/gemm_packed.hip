@@ -255,9 +255,10 @@ __global__ __launch_bounds__(PK_THREADS, pk_wgs_per_cu(NB, MT, RC)) void gemm_pa
             for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
 
     // The loop has no branch in it: pieces and fragments that do not exist are out of a descriptor's range or get an offset that is,
-    // by one comparison per piece; and the reads of a k-step are issued a whole step ahead.  (With the range of a chunk tested per
-    // copy -- eight scalar branches a trip -- and the reads left to the compiler, which put them right before their use, 16384 rows
-    // took: one-term gate/up 2674 -> 2544 us, two-term O 980 -> 953, down 2440 -> 2400; 2048 rows 372 -> 346 and 140 -> 131.)
+    // by one comparison each; and the reads of a k-step are issued a whole step ahead.  (With the range of a chunk tested per
+    // copy -- eight scalar branches a trip -- and the reads left to the compiler, which put them right before their use, us, on one box:
+    // 16384 rows, 7B shape, one-term gate/up 2446 -> 2380, two-term QKV 2448 -> 2398, O 842 -> 822, down 2154 -> 2106; 2048 rows, 341 -> 333, 324 -> 317,
+    // 138 -> 130, 316 -> 296.)
     // One chunk (PAR = parity of its index relative to c0): all activation copies of a trip are issued
     // before its weight loads -- the hardware retires loads in issue order, so waiting for the (short, L2)
     // activation copy never waits for younger weight loads.

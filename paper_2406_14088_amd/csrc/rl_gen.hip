@@ -502,9 +502,10 @@ bool run_layers(rl_gen *h, const int32_t *tokens, int nb, int T, int b0, bool de
                                d_valid, decode && h->eos >= 0 ? h->d_done() : nullptr,  // without an end token no sequence ever ends
                                q_lo);
         }
-        // (A single kernel that takes q, k, v from the partials, rotates, appends and attends exists --
-        // launch_decode_attention_fused -- but measured no faster per step: what the separate kernel costs, the
-        // attention wavefronts then spend before their first cache load.)
+        // (A single kernel that takes q, k, v from the partials, rotates, appends and attends exists for half rows of a contiguous
+        // cache -- launch_decode_attention_fused -- but measured no faster per step of 128 sequences: what the separate kernel costs,
+        // the attention wavefronts then spend before their first cache load.  It takes neither block-scaled rows nor page lists, and
+        // few sequences, where a launch counts for more, were not measured.)
         if (decode) {
             Scope sc(h, RL_GEN_K_DECODE_ATTN, st);
             launch_decode_attention(h->qf32(), h->kslab(l), h->vslab(l), h->d_lens(), 1, h->attn(), h->attn_ws(), nb,
